@@ -169,27 +169,29 @@ size_t hd_model_packed_bytes(int64_t F, int64_t D, int64_t K, hd_dtype dt) {
 }
 
 // Workspace one call needs: with a packed model or raw matrices, in the
-// default or the deterministic mode (the size queries cover both modes).
+// default or the deterministic mode (the size queries cover both modes), at
+// least (query false) or for its fastest plan (query true).
 static size_t workspace_need(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool packed,
-                             bool det) {
+                             bool det, bool query = false) {
   const Route r = route(N, F, D, K, dt, packed);
+  const auto large = query ? hd::large_workspace_bytes : hd::large_workspace_min;
   if ((r == Route::kSmall || r == Route::kSmallChunked) && dt == HD_I8) {
     // an unaligned X takes the large-batch kernels instead
     const size_t s = hd::small_workspace_bytes(small_n(r, N), F, D, K, dt, det);
-    const size_t l = hd::large_workspace_bytes(N, F, D, K, dt);
+    const size_t l = large(N, F, D, K, dt);
     return s > l ? s : l;
   }
   if (r == Route::kSmall || r == Route::kSmallChunked)
     return hd::small_workspace_bytes(small_n(r, N), F, D, K, dt, det);
-  if (packed) return hd::large_workspace_bytes(N, F, D, K, dt);
-  return align256(hd::large_workspace_bytes(N, F, D, K, dt)) +
+  if (packed) return large(N, F, D, K, dt);
+  return align256(large(N, F, D, K, dt)) +
          align256(hd::large_packed_bytes(F, D, K, dt));
 }
 
 static size_t workspace_query(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool packed) {
   if (N < 1 || F < 1 || D < 1 || K < 1 || !enums_ok(dt, 0) || !dims_ok(N, F, D, K)) return 0;
-  const size_t a = workspace_need(N, F, D, K, dt, packed, false);
-  const size_t b = workspace_need(N, F, D, K, dt, packed, true);
+  const size_t a = workspace_need(N, F, D, K, dt, packed, false, true);
+  const size_t b = workspace_need(N, F, D, K, dt, packed, true, true);
   return a > b ? a : b;
 }
 
@@ -261,21 +263,24 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
     if (workspace_bytes < plan_ws) return HD_ERR_WORKSPACE;
     if (dry) return HD_OK;
     return from_hip(
-        hd::launch_large(X, packed, labels, scores, N, F, D, K, dt, act, workspace, stream));
+        hd::launch_large(X, packed, labels, scores, N, F, D, K, dt, act, workspace,
+                         workspace_bytes, stream));
   }
   // Raw matrices: the scratch that must start at zero (tile counters, split-D
   // partial scores) stays at offset 0, the same place every route keeps it, and
   // the packed copy of B and C goes after it. The copy is cleared again once
   // the kernel has read it, so the whole workspace is zero after the call and
   // can be reused by a call of any shape.
-  const size_t zone = align256(hd::large_workspace_bytes(N, F, D, K, dt));
+  // (the fastest plan's scratch when the workspace has room for it)
+  size_t zone = align256(hd::large_workspace_bytes(N, F, D, K, dt));
   const size_t pb = hd::large_packed_bytes(F, D, K, dt);
+  if (workspace_bytes < zone + pb) zone = align256(hd::large_workspace_min(N, F, D, K, dt));
   if (plan_ws > zone || workspace_bytes < zone + pb) return HD_ERR_WORKSPACE;
   if (dry) return HD_OK;
   char* copy = static_cast<char*>(workspace) + zone;
   if (hd::launch_pack(B, C, F, D, K, dt, copy, stream) != hipSuccess) return HD_ERR_HIP;
   const hipError_t e =
-      hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace, stream);
+      hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace, zone, stream);
   if (e != hipSuccess) return HD_ERR_HIP;
   return from_hip(hd::launch_zero(copy, pb, stream));
 }
@@ -428,7 +433,12 @@ hd_status hd_infer_packed_noalloc(const void* X, const void* packed, int32_t* la
   // (or a caller that wrote the memory) would leave it otherwise: clear the
   // part this call uses with a fill kernel (not a memset node, so the call
   // can be captured in a graph).
-  if (need > 0 && hd::launch_zero(ws, need, stream) != hipSuccess) return HD_ERR_HIP;
+  size_t used = need;
+  if (route(N, F, D, K, dt, true) == Route::kLarge) {
+    const size_t l = hd::large_workspace_used(X, N, F, D, K, dt, act_base(act), kScratchBytes);
+    used = l > used ? l : used;
+  }
+  if (used > 0 && hd::launch_zero(ws, used, stream) != hipSuccess) return HD_ERR_HIP;
   return infer_common(X, nullptr, nullptr, packed, labels, scores, N, F, D, K, dt, act, ws,
                       kScratchBytes, stream);
 }

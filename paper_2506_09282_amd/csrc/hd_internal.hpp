@@ -104,13 +104,18 @@ bool large_supported(int64_t N, int64_t F, int64_t D, int64_t K, int dt);
 const char* large_kernel_name(int64_t N, int64_t F, int64_t D, int64_t K, int dt);
 size_t large_packed_bytes(int64_t F, int64_t D, int64_t K, int dt);
 // Workspace of the large-batch kernels: for the plan taken with X 16-byte
-// aligned (x16) or not, and the larger of the two (what the size query gives).
+// aligned (x16) or not; the larger of the two (what a call needs at least);
+// what the size query gives (enough for the fastest plan); and what a call
+// with ws_bytes of workspace uses.
 size_t large_workspace_bytes_for(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool x16);
+size_t large_workspace_min(int64_t N, int64_t F, int64_t D, int64_t K, int dt);
 size_t large_workspace_bytes(int64_t N, int64_t F, int64_t D, int64_t K, int dt);
+size_t large_workspace_used(const void* X, int64_t N, int64_t F, int64_t D, int64_t K, int dt,
+                            int act, size_t ws_bytes);
 hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64_t K, int dt,
                        void* packed, hipStream_t stream);
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
-                        void* workspace, hipStream_t stream);
+                        void* workspace, size_t ws_bytes, hipStream_t stream);
 
 }  // namespace hd

@@ -29,15 +29,14 @@
 // of each sample tile (ticket counter, self-cleaning).
 #include <type_traits>
 
-#include "hd_common.hpp"
-#include "hd_internal.hpp"
+#include "hd_large.hpp"
 
 namespace hd {
 
+using namespace lg;
+
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;
 // f-steps of B fragments in flight per wave: deeper while registers allow
 constexpr int prefetch_of(int ntiles, int kb) { return ntiles * kb <= 4 ? 8 : 4; }
 // Ring depth of the int8 resident-X kernel where 8 would be used: a unit's
@@ -50,177 +49,6 @@ constexpr int fused_prefetch(int nfs) {
   return pad10 < pad8 ? 10 : 8;
 }
 constexpr int kMaxSlices = 64;  // D slices per sample tile (split-D)
-constexpr int kLdsBytes = 160 * 1024 - 256;  // leave room for static LDS
-
-template <typename U, typename V>
-__device__ __forceinline__ U bitcast(const V& v) {
-  static_assert(sizeof(U) == sizeof(V), "size");
-  U u;
-  __builtin_memcpy(&u, &v, sizeof(U));
-  return u;
-}
-
-// ---------------------------------------------------------------------------
-// Element-type traits. One "f-step" consumes one 16-byte fragment per lane of
-// both operands: 16 features for bf16 (one 32x32x16 MFMA), 8 features for
-// fp32 (four 32x32x2 MFMAs).
-// ---------------------------------------------------------------------------
-struct TrBF16 {
-  typedef bf16raw elem;
-  static constexpr int kFStep = 16;
-  static constexpr int kVec = 8;  // elements per 16-byte group
-  static constexpr int kEsz = 2;
-  // element e of a 16-byte group held as four dwords: set, read, clear
-  __device__ static void put(uint32_t (&t)[4], int e, elem x) {
-    t[e >> 1] |= (uint32_t)x << (16 * (e & 1));
-  }
-  __device__ static elem get(const uint32_t (&t)[4], int e) {
-    return (uint16_t)(t[e >> 1] >> (16 * (e & 1)));
-  }
-  __device__ static void clear(uint32_t (&t)[4], int e) { t[e >> 1] &= ~(0xffffu << (16 * (e & 1))); }
-  // Stage I accumulator value v is >= 0 (the HardSign test, Eq. 1)
-  __device__ static bool nonneg(float v) { return v >= 0.0f; }
-  static constexpr int kStage1Mfma = 1;  // matrix instructions per stage1 call
-  static constexpr int kCFrags = 2;  // 1 KiB C fragments per (d-block, class block)
-  // LDS position of feature column c inside a sample row.
-  __device__ static int lds_pos(int c) { return c; }
-  __device__ static void stage1(f32x16& acc, const uint4& a, const uint4& b) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast<bf16x8>(a), bitcast<bf16x8>(b), acc,
-                                                  0, 0, 0);
-  }
-  // first step of a sum: the instruction's accumulator input is the constant 0
-  __device__ static void stage1_init(f32x16& acc, const uint4& a, const uint4& b) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast<bf16x8>(a), bitcast<bf16x8>(b),
-                                                  f32x16{}, 0, 0, 0);
-  }
-};
-
-struct TrF32 {
-  typedef float elem;
-  static constexpr int kFStep = 8;
-  static constexpr int kVec = 4;
-  static constexpr int kEsz = 4;
-  __device__ static void put(uint32_t (&t)[4], int e, elem x) { t[e] = __float_as_uint(x); }
-  __device__ static elem get(const uint32_t (&t)[4], int e) { return __uint_as_float(t[e]); }
-  __device__ static void clear(uint32_t (&t)[4], int e) { t[e] = 0u; }
-  __device__ static bool nonneg(float v) { return v >= 0.0f; }
-  static constexpr int kStage1Mfma = 4;
-  static constexpr int kCFrags = 4;
-  // Within each group of 8 features the even ones are stored first, so a
-  // lane of MFMA k-half g reads its four features (g, g+2, g+4, g+6) as one
-  // 16-byte word.
-  __device__ static int lds_pos(int c) {
-    const int r = c & 7;
-    return (c & ~7) + 4 * (r & 1) + (r >> 1);
-  }
-  __device__ static void stage1(f32x16& acc, const uint4& a, const uint4& b) {
-    const float4 af = bitcast<float4>(a), bf = bitcast<float4>(b);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.x, bf.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.y, bf.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.z, bf.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.w, bf.w, acc, 0, 0, 0);
-  }
-  __device__ static void stage1_init(f32x16& acc, const uint4& a, const uint4& b) {
-    const float4 af = bitcast<float4>(a), bf = bitcast<float4>(b);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.x, bf.x, f32x16{}, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.y, bf.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.z, bf.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af.w, bf.w, acc, 0, 0, 0);
-  }
-};
-
-// int8 model variant: X and B int8, Stage I on the int8 matrix instruction
-// with exact int32 accumulation (the accumulator registers hold the int32
-// bits), HardSign on the exact integer; Stage II takes C widened to bf16
-// (exact for |c| <= 128) through the bf16 path. One f-step is 32 features.
-struct TrI8 {
-  typedef int8_t elem;
-  static constexpr int kFStep = 32;
-  static constexpr int kVec = 16;
-  static constexpr int kEsz = 1;
-  static constexpr int kStage1Mfma = 1;
-  static constexpr int kCFrags = 2;  // C tiles are the bf16 ones
-  __device__ static void put(uint32_t (&t)[4], int e, elem x) {
-    t[e >> 2] |= (uint32_t)(uint8_t)x << (8 * (e & 3));
-  }
-  __device__ static elem get(const uint32_t (&t)[4], int e) {
-    return (int8_t)(uint8_t)(t[e >> 2] >> (8 * (e & 3)));
-  }
-  __device__ static void clear(uint32_t (&t)[4], int e) { t[e >> 2] &= ~(0xffu << (8 * (e & 3))); }
-  __device__ static bool nonneg(float v) { return __float_as_int(v) >= 0; }
-  __device__ static int lds_pos(int c) { return c; }
-  __device__ static void stage1(f32x16& acc, const uint4& a, const uint4& b) {
-    acc = bitcast<f32x16>(__builtin_amdgcn_mfma_i32_32x32x32_i8(
-        bitcast<i32x4>(a), bitcast<i32x4>(b), bitcast<i32x16>(acc), 0, 0, 0));
-  }
-  __device__ static void stage1_init(f32x16& acc, const uint4& a, const uint4& b) {
-    acc = bitcast<f32x16>(
-        __builtin_amdgcn_mfma_i32_32x32x32_i8(bitcast<i32x4>(a), bitcast<i32x4>(b), i32x16{}, 0, 0, 0));
-  }
-};
-
-// Largest sizes of the int8 variant for which every sum is exact: |V| <=
-// 128 * 128 * F < 2^31 in int32, and |S| <= 128 * D <= 2^24 in fp32.
-constexpr int64_t kI8MaxF = (int64_t(1) << 17) - 1;
-constexpr int64_t kI8MaxD = int64_t(1) << 17;
-
-// LDS row padding of an X tile: one 16-byte group (keeps the 32 rows read by
-// one fragment load on distinct LDS banks).
-template <class Tr>
-constexpr int pad_of() {
-  return 16 / Tr::kEsz;
-}
-
-// Number of f-steps and padded row pitch (elements) of the LDS X tile.
-template <class Tr>
-__host__ __device__ inline int nfs_of(int F) {
-  return (F + Tr::kFStep - 1) / Tr::kFStep;
-}
-template <class Tr>
-__host__ __device__ inline int pitch_of(int F) {
-  // Padding by half a 16-byte group (bf16) / one group (fp32) keeps the
-  // 32 rows read by one fragment load on distinct LDS banks.
-  return nfs_of<Tr>(F) * Tr::kFStep + pad_of<Tr>();
-}
-
-// ---------------------------------------------------------------------------
-// Tiled model image.
-//   B tile (db, fs): 64 lanes x 16 bytes; lane l holds
-//     bf16: B[16fs + 8(l/32) + e][32db + l%32], e = 0..7
-//     fp32: B[8fs + 2j + l/32][32db + l%32],   j = 0..3
-//   C tile, bf16 (db, h, kb): lane l holds C[32kb + l%32][32db + 16h + 4(l/32) + e]
-//     for e = 0..3 and C[..][32db + 16h + 8 + 4(l/32) + e - 4] for e = 4..7
-//   C tile, fp32 (db, kb, q): lane l holds C[32kb + l%32][32db + 8q + 4(l/32) + j]
-// Out-of-range entries are zero. NDB is rounded up to even (64-dim units).
-// ---------------------------------------------------------------------------
-struct PackGeom {
-  int ndb, nfs, kb;
-  size_t b_bytes, c_bytes;
-};
-
-// Class blocks of 32 handled per launch: 1, 2 or 4.
-inline int kb_of(int64_t K) {
-  const int kb = (int)cdiv(K, 32);
-  return kb == 3 ? 4 : kb;
-}
-
-// Sample tiles per workgroup of the F-chunked kernel: 4 when the accumulators
-// fit in registers, fewer as class blocks grow.
-template <class Tr>
-constexpr int chunk_ntiles(int kb) {
-  return kb > 2 ? (Tr::kEsz <= 2 ? 2 : 1) : kb == 2 ? 2 : 4;
-}
-
-template <class Tr>
-PackGeom pack_geom(int64_t F, int64_t D, int64_t K) {
-  PackGeom g;
-  g.ndb = (int)(cdiv(D, 64) * 2);
-  g.nfs = nfs_of<Tr>((int)F);
-  g.kb = kb_of(K);
-  g.b_bytes = (size_t)g.ndb * g.nfs * 1024;
-  g.c_bytes = (size_t)g.ndb * g.kb * Tr::kCFrags * 1024;
-  return g;
-}
 
 __global__ void pack_b_bf16(const bf16raw* __restrict__ B, uint4* __restrict__ Bp, int F, int D,
                             int ndb, int nfs) {
@@ -333,159 +161,15 @@ __global__ void pack_c_f32(const float* __restrict__ C, uint4* __restrict__ Cp, 
                                  __float_as_uint(v[2]), __float_as_uint(v[3]));
 }
 
-// ---------------------------------------------------------------------------
-// Stage II on one finished 32x32 V^T tile (rows d of block db, columns n of
-// one sample tile): activation, then accumulate S^T for every class block.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
-  // round-to-nearest-even fp32 -> bf16 for finite values
-  uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-  ua = (ua + 0x7fffu + ((ua >> 16) & 1u)) >> 16;
-  ub = (ub + 0x7fffu + ((ub >> 16) & 1u)) >> 16;
-  return ua | (ub << 16);
-}
-
-__device__ __forceinline__ uint32_t sign_pair(float a, float b) {
-  const uint32_t lo = a >= 0.0f ? 0x3F80u : 0xBF80u;
-  const uint32_t hi = b >= 0.0f ? 0x3F80u : 0xBF80u;
-  return lo | (hi << 16);
-}
-
-template <int KB, int ACT>
-__device__ __forceinline__ void stage2_bf16(const f32x16& v, const uint4 (&cfr)[2][KB],
-                                            f32x16 (&s)[KB]) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if constexpr (ACT == 0) {
-      uint4 hb;
-      hb.x = sign_pair(v[8 * h + 0], v[8 * h + 1]);
-      hb.y = sign_pair(v[8 * h + 2], v[8 * h + 3]);
-      hb.z = sign_pair(v[8 * h + 4], v[8 * h + 5]);
-      hb.w = sign_pair(v[8 * h + 6], v[8 * h + 7]);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast<bf16x8>(cfr[h][kb]),
-                                                        bitcast<bf16x8>(hb), s[kb], 0, 0, 0);
-    } else {
-      // Identity test mode: split v into three bf16 terms (about 24 bits).
-      float r[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = v[8 * h + e];
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        uint4 hb;
-        hb.x = pack2_bf16(r[0], r[1]);
-        hb.y = pack2_bf16(r[2], r[3]);
-        hb.z = pack2_bf16(r[4], r[5]);
-        hb.w = pack2_bf16(r[6], r[7]);
-        const uint32_t w[4] = {hb.x, hb.y, hb.z, hb.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t bits = (w[e >> 1] >> (16 * (e & 1))) & 0xffffu;
-          r[e] -= __uint_as_float(bits << 16);
-        }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast<bf16x8>(cfr[h][kb]),
-                                                          bitcast<bf16x8>(hb), s[kb], 0, 0, 0);
-      }
-    }
-  }
-}
-
-template <int KB, int ACT>
-__device__ __forceinline__ void stage2_f32(const f32x16& v, const uint4 (&cfr)[KB][4],
-                                           f32x16 (&s)[KB]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float h = ACT ? v[4 * q + j] : hardsign(v[4 * q + j]);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const float c = __uint_as_float(j == 0 ? cfr[kb][q].x
-                                         : j == 1 ? cfr[kb][q].y
-                                         : j == 2 ? cfr[kb][q].z
-                                                  : cfr[kb][q].w);
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(c, h, s[kb], 0, 0, 0);
-      }
-    }
-  }
-}
-
-// C fragments of one 64-dim unit (two d-blocks).
-template <class Tr, int KB>
-struct CFrags;
-template <int KB>
-struct CFrags<TrBF16, KB> {
-  uint4 f[2][2][KB];  // [db2][h][kb]
-  __device__ void load(const uint4* __restrict__ Cp, int db0, int lane) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-          f[b][h][kb] = Cp[((int64_t)((db0 + b) * 2 + h) * KB + kb) * 64 + lane];
-  }
-  template <int ACT>
-  __device__ void apply(const f32x16& v, int b, f32x16 (&s)[KB]) const {
-    stage2_bf16<KB, ACT>(v, f[b], s);
-  }
-};
-template <int KB>
-struct CFrags<TrF32, KB> {
-  uint4 f[2][KB][4];  // [db2][kb][q]
-  __device__ void load(const uint4* __restrict__ Cp, int db0, int lane) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          f[b][kb][q] = Cp[(((int64_t)(db0 + b) * KB + kb) * 4 + q) * 64 + lane];
-  }
-  template <int ACT>
-  __device__ void apply(const f32x16& v, int b, f32x16 (&s)[KB]) const {
-    stage2_f32<KB, ACT>(v, f[b], s);
-  }
-};
-
-template <int KB>
-struct CFrags<TrI8, KB> : CFrags<TrBF16, KB> {
-  template <int ACT>
-  __device__ void apply(const f32x16& v, int b, f32x16 (&s)[KB]) const {
-    f32x16 vf;  // the exact int32 sums as floats (sign and zero preserved)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) vf[r] = (float)__float_as_int(v[r]);
-    stage2_bf16<KB, ACT>(vf, this->f[b], s);
-  }
-};
-
-struct LargeWs {
-  unsigned* counters;  // [ntiles]
-  float* part;         // [DS][N][K]
-};
-
-__host__ __device__ inline LargeWs large_ws(void* ws, int64_t ntiles) {
-  LargeWs w;
-  w.counters = reinterpret_cast<unsigned*>(ws);
-  const size_t cbytes = ((size_t)ntiles * sizeof(unsigned) + 255) / 256 * 256;
-  w.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + cbytes);
-  return w;
-}
-
 // Combine the waves' partial scores through LDS, then argmax (Eq. 9) and
-// write; with a split of D, publish this slice's partial scores and let the
-// tile's last slice finish (fixed slice order, so results are deterministic).
+// write; with a split of D, leave this slice's partial scores for
+// reduce_slices_kernel.
 template <int NTILES, int KB>
-__device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds, int* s_last_p,
+__device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds,
                             int32_t* __restrict__ labels, float* __restrict__ scores, int N, int K,
-                            int DS, int ntiles, int slice, int tile, int n0,
-                            void* __restrict__ workspace) {
+                            int DS, int slice, int n0, void* __restrict__ workspace) {
   constexpr int NT = 32 * NTILES;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int& s_last = *s_last_p;
   __syncthreads();  // X tile no longer needed
   float* sred = reinterpret_cast<float*>(lds);  // [kWaves][NT][32*KB]
   constexpr int KP = 32 * KB;
@@ -519,52 +203,62 @@ __device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds, int*
     }
     return;
   }
-  // Split-D: publish this slice's partial, the last slice of the tile finishes
-  // (summing the slices in a fixed order, so results are deterministic).
-  const LargeWs ws = large_ws(workspace, ntiles);
-  float* mypart = ws.part + (int64_t)slice * N * K;
+  float* mypart = slice_part(workspace, slice, N, K) + (int64_t)n0 * K;
   for (int i = tid; i < rows * K; i += kThreads) {
     const int n = i / K, k = i - n * K;
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) s += sred[((int64_t)w * NT + n) * KP + k];
-    publish_store(mypart + (int64_t)(n0 + n) * K + k, s);
+    mypart[i] = s;
   }
-  wait_own_memory_ops();
-  __syncthreads();
-  if (tid == 0) s_last = (take_ticket(ws.counters + tile) == (unsigned)DS - 1) ? 1 : 0;
-  __syncthreads();
-  if (!s_last) return;
-  for (int i = tid; i < rows * K; i += kThreads) {
-    const int n = i / K, k = i - n * K;
+}
+
+// Second launch of a call with D split into ds slices: sums the slices'
+// partial scores in slice order (results do not depend on timing), writes the
+// scores, takes the row argmax (lowest index on ties) and clears the
+// workspace again. One thread per (sample, class), 256 / K whole rows per
+// workgroup, 16 slices' loads in flight. A last-arriver reduction inside the
+// main kernel has one workgroup per sample tile read every slice with
+// returning atomics: at N = 4096, F = 617, K = 26 (bf16, 16 slices) that call
+// took 135 us.
+__global__ __launch_bounds__(256) void reduce_slices_kernel(float* __restrict__ part,
+                                                            int32_t* __restrict__ labels,
+                                                            float* __restrict__ scores, int N,
+                                                            int K, int ds) {
+  __shared__ float row[256];
+  const int rpw = 256 / K, tid = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * rpw * K, total = (int64_t)N * K;
+  const int64_t i = i0 + tid;
+  if (tid < rpw * K && i < total) {
     float s = 0.0f;
-    // slices in groups of 16 whose reads are all in flight together
-    for (int sl0 = 0; sl0 < DS; sl0 += 16) {
+    for (int sl0 = 0; sl0 < ds; sl0 += 16) {
       float t[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        t[j] = sl0 + j < DS ? take_and_clear(ws.part + ((int64_t)(sl0 + j) * N + n0 + n) * K + k)
-                            : 0.0f;
+      for (int j = 0; j < 16; ++j) t[j] = sl0 + j < ds ? part[(sl0 + j) * total + i] : 0.0f;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) s += t[j];
+      for (int j = 0; j < 16; ++j)
+        if (sl0 + j < ds) {
+          s += t[j];
+          part[(sl0 + j) * total + i] = 0.0f;
+        }
     }
-    sred[i] = s;  // the per-wave partials are no longer needed
+    row[tid] = s;
+    if (scores) scores[i] = s;
   }
   __syncthreads();
-  for (int n = tid; n < rows; n += kThreads) {
-    float best = 0.0f;
+  const int64_t n = (int64_t)blockIdx.x * rpw + tid;
+  if (tid < rpw && n < N) {
+    float best = row[tid * K];
     int best_k = 0;
-    for (int k = 0; k < K; ++k) {
-      const float s = sred[n * K + k];
-      if (scores) scores[(int64_t)(n0 + n) * K + k] = s;
-      if (k == 0 || s > best) {
+    for (int k = 1; k < K; ++k) {
+      const float s = row[tid * K + k];
+      if (s > best) {
         best = s;
         best_k = k;
       }
     }
-    labels[n0 + n] = best_k;
+    labels[n] = best_k;
   }
-  if (tid == 0) reset_counter(ws.counters + tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -580,12 +274,10 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel(
   static_assert(PF % 2 == 0, "X fragments are double-buffered by step parity");
   constexpr int kPrefetch = PF;  // B ring depth in f-steps
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nfs = nfs_of<Tr>(F);
   const int pitch = pitch_of<Tr>(F);  // elements
-  const int ntiles = (int)cdiv(N, NT);
   // Consecutive workgroups take different D slices, so with round-robin
   // dispatch over the XCDs each XCD's L2 serves one slice of B.
   const int slice = blockIdx.x % DS;
@@ -778,8 +470,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel(
       for (int t = 0; t < NTILES; ++t) cf.template apply<ACT>(vacc[b][t], b, sacc[t]);
   }
 
-  finish_tile<NTILES, KB>(sacc, lds, &s_last, labels, scores, N, K, DS, ntiles, slice, tile, n0,
-                          workspace);
+  finish_tile<NTILES, KB>(sacc, lds, labels, scores, N, K, DS, slice, n0, workspace);
 }
 
 // ---------------------------------------------------------------------------
@@ -800,13 +491,11 @@ __global__ __launch_bounds__(kThreads, 1) void large_chunked_kernel(
   constexpr int kPrefetch = prefetch_of(NTILES, KB);
   constexpr int kSB = 8;  // staging items per thread per batch
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nfs = nfs_of<Tr>(F);
   const int nchunks = (nfs + fsc - 1) / fsc;
   const int pitch = fsc * Tr::kFStep + pad_of<Tr>();  // elements
-  const int ntiles = (int)cdiv(N, NT);
   const int slice = blockIdx.x % DS;
   const int tile = blockIdx.x / DS;
   const int n0 = tile * NT;
@@ -964,8 +653,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_chunked_kernel(
     }
   }
   __syncthreads();  // the last chunk's readers are done before LDS is reused
-  finish_tile<NTILES, KB>(sacc, lds, &s_last, labels, scores, N, K, DS, ntiles, slice, tile, n0,
-                          workspace);
+  finish_tile<NTILES, KB>(sacc, lds, labels, scores, N, K, DS, slice, n0, workspace);
 }
 
 // LDS fragment reads of the double-buffered kernel. With buffer-to-LDS loads
@@ -1051,13 +739,11 @@ __global__ __launch_bounds__(kThreads, 1) void large_chunked_dma_kernel(
   // s_waitcnt immediate: vmcnt(kWait), expcnt and lgkmcnt not waited on
   constexpr int kWaitImm = 0x0F70 | (kWait & 15) | ((kWait >> 4) << 14);
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nfs = nfs_of<Tr>(F);
   const int nchunks = (nfs + FSC - 1) / FSC;
   const int nfl = nchunks * FSC;  // f-steps per unit, padded to whole chunks
-  const int ntiles = (int)cdiv(N, NT);
   const int slice = blockIdx.x % DS;
   const int tile = blockIdx.x / DS;
   const int n0 = tile * NT;
@@ -1209,8 +895,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_chunked_dma_kernel(
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // no load into LDS is still in flight
   __syncthreads();
-  finish_tile<NTILES, KB>(sacc, lds, &s_last, labels, scores, N, K, DS, ntiles, slice, tile, n0,
-                          workspace);
+  finish_tile<NTILES, KB>(sacc, lds, labels, scores, N, K, DS, slice, n0, workspace);
 }
 
 // ---------------------------------------------------------------------------
@@ -1802,20 +1487,29 @@ template <class Tr, int NTILES, int KB>
 hipError_t launch_cfg(const LargeCfg& c, const void* X, const uint4* Bp, const uint4* Cp,
                       int32_t* labels, float* scores, int64_t N, int64_t F, int64_t K, int ndb,
                       int act, void* ws, hipStream_t stream) {
-  if (act)
-    return launch_act<Tr, NTILES, KB, 1>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
-  return launch_act<Tr, NTILES, KB, 0>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
+  const hipError_t e =
+      act ? launch_act<Tr, NTILES, KB, 1>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream)
+          : launch_act<Tr, NTILES, KB, 0>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
+  if (e != hipSuccess || c.ds == 1) return e;
+  return launch_reduce_slices(ws, labels, scores, N, K, c.ds, stream);
 }
 
 template <class Tr>
 hipError_t launch_tr(const void* X, const void* packed, int32_t* labels, float* scores,
                      int64_t N, int64_t F, int64_t D, int64_t K, int act, void* ws,
-                     hipStream_t stream) {
+                     size_t ws_bytes, hipStream_t stream) {
   const LargeCfg c = large_cfg<Tr>(N, F, D, K, ((uintptr_t)X % 16) == 0);
   if (!c.ok) return hipErrorInvalidValue;
   const PackGeom g = pack_geom<Tr>(F, D, K);
   const uint4* Bp = (const uint4*)packed;
   const uint4* Cp = (const uint4*)((const char*)packed + g.b_bytes);
+  if constexpr (Tr::kEsz <= 2) {
+    constexpr int dt = Tr::kEsz == 2 ? 1 : 2;
+    const XregPlan p = xreg_plan(N, F, D, K, dt, act, (uintptr_t)X % 4 == 0, ws_bytes);
+    if (p.ok)
+      return launch_xreg(p, XregArgs{X, Bp, Cp, labels, scores, (int)F, (int)K, g.ndb, ws, stream},
+                         N, dt);
+  }
   const int nt = c.ntiles_per_wg, kb = c.kb;
 #define HD_LAUNCH(NTV, KBV)                                                                       \
   if (nt == NTV && kb == KBV)                                                                     \
@@ -1921,6 +1615,15 @@ hipError_t launch_bundle_dma(const BundleCfg& c, const void* X, const void* pack
 
 }  // namespace
 
+namespace lg {
+hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
+                                int ds, hipStream_t stream) {
+  hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)cdiv(N, 256 / K)), dim3(256), 0, stream,
+                     (float*)ws, labels, scores, (int)N, (int)K, ds);
+  return hipGetLastError();
+}
+}  // namespace lg
+
 bool bundle_packed_supported(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
   return with_traits(dt, [&](auto tr) { return bundle_cfg<decltype(tr)>(N, F, D, K).ok; });
 }
@@ -2006,11 +1709,25 @@ size_t large_workspace_bytes_for(int64_t N, int64_t F, int64_t D, int64_t K, int
 }
 
 // The plan (tile size, D slices) depends on whether X is 16-byte aligned, which
-// the size query does not know: size for the larger of the two plans.
-size_t large_workspace_bytes(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
+// the size query does not know: size for the larger of the two plans. This is
+// what a call needs at least; the kernel with X in registers takes its split
+// of D from the workspace there is, and the size query covers its best one.
+size_t large_workspace_min(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
   const size_t a = large_workspace_bytes_for(N, F, D, K, dt, true);
   const size_t b = large_workspace_bytes_for(N, F, D, K, dt, false);
   return a > b ? a : b;
+}
+
+size_t large_workspace_bytes(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
+  const size_t a = large_workspace_min(N, F, D, K, dt);
+  const size_t b = xreg_plan(N, F, D, K, dt, 0, true, ~size_t(0)).ws;
+  return a > b ? a : b;
+}
+
+size_t large_workspace_used(const void* X, int64_t N, int64_t F, int64_t D, int64_t K, int dt,
+                            int act, size_t ws_bytes) {
+  const XregPlan p = xreg_plan(N, F, D, K, dt, act, (uintptr_t)X % 4 == 0, ws_bytes);
+  return p.ok ? p.ws : large_workspace_bytes_for(N, F, D, K, dt, (uintptr_t)X % 16 == 0);
 }
 
 hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64_t K, int dt,
@@ -2045,12 +1762,11 @@ hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64
 
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
-                        void* workspace, hipStream_t stream) {
-  if (dt == 0)
-    return launch_tr<TrF32>(X, packed, labels, scores, N, F, D, K, act, workspace, stream);
-  if (dt == 2)
-    return launch_tr<TrI8>(X, packed, labels, scores, N, F, D, K, act, workspace, stream);
-  return launch_tr<TrBF16>(X, packed, labels, scores, N, F, D, K, act, workspace, stream);
+                        void* workspace, size_t ws_bytes, hipStream_t stream) {
+  return with_traits(dt, [&](auto tr) {
+    return launch_tr<decltype(tr)>(X, packed, labels, scores, N, F, D, K, act, workspace,
+                                   ws_bytes, stream);
+  });
 }
 
 }  // namespace hd
