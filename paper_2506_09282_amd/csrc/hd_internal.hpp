@@ -92,6 +92,13 @@ hipError_t launch_bundle_packed(const void* X, const void* packed, const int32_t
                                 int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K,
                                 int dt, hipStream_t stream);
 
+// The kernel with B in registers (hd_train_breg.hip): whether it takes these
+// sizes, and its launch.
+bool bundle_breg_ok(const void* X, int64_t N, int64_t F, int64_t D, int64_t K, int dt);
+hipError_t launch_bundle_breg(const void* X, const void* packed, const int32_t* y,
+                              int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K, int dt,
+                              hipStream_t stream);
+
 // Unfused stages.
 hipError_t launch_encode(const void* X, const void* B, float* H, int64_t N, int64_t F, int64_t D,
                          int dt, int act, hipStream_t stream);

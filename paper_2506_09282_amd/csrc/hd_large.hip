@@ -660,9 +660,6 @@ __global__ __launch_bounds__(kThreads, 1) void large_chunked_kernel(
 // in flight the compiler would put a full vmcnt(0) wait before every LDS
 // read it cannot prove disjoint from them; these reads are issued directly
 // and completed by an explicit lgkmcnt(0) tied to the destination registers.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 lds_read16_issue(uint32_t addr) {
   u32x4_t v;
@@ -1644,6 +1641,8 @@ hipError_t launch_bundle_packed(const void* X, const void* packed, const int32_t
                                 int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K,
                                 int dt, hipStream_t stream) {
   const dim3 block(kThreads);
+  if (bundle_breg_ok(X, N, F, D, K, dt))
+    return launch_bundle_breg(X, packed, y, counts, N, F, D, K, dt, stream);
   if (dt == 0) {
     const BundleCfg c = bundle_cfg<TrF32>(N, F, D, K);
     if (!c.ok) return hipErrorInvalidValue;

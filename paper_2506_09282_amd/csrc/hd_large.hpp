@@ -312,6 +312,48 @@ struct CFrags<TrI8, KB> : CFrags<TrBF16, KB> {
   }
 };
 
+// The value of the lane 32 away.
+__device__ __forceinline__ uint32_t swap_halves(uint32_t v) {
+  return (uint32_t)__shfl_xor((int)v, 32, kWave);
+}
+
+// LDS byte address of a pointer into the dynamic LDS array.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+typedef int rsrc_t __attribute__((ext_vector_type(4)));
+
+// 1 KiB from global memory straight into LDS: lane l's 16 bytes at byte offset
+// `off` of the buffer land at lds + 16 l; offsets past the buffer's end
+// deliver zeros. Issued as assembly so that the compiler does not take every
+// later LDS read for one that may overlap it (it would wait for all loads
+// before each read); it writes no register, and the waits are explicit.
+__device__ __forceinline__ void dma_1k(rsrc_t rsrc, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(lds), "v"(off), "s"(rsrc)
+               : "memory");
+}
+
+// The same with 4 bytes per lane.
+__device__ __forceinline__ void dma_256(rsrc_t rsrc, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+               :
+               : "s"(lds), "v"(off), "s"(rsrc)
+               : "memory");
+}
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  rsrc_t r;
+  r.x = (int)(uint32_t)a;
+  r.y = (int)(uint32_t)(a >> 32);
+  r.z = (int)bytes;
+  r.w = 0x00020000;
+  return r;
+}
+
 // Split of D: slice s writes its partial scores to part[s][N][K] at the start
 // of the workspace with plain stores; a second launch (hd_large.hip) sums the
 // slices in a fixed order, takes the argmax and clears what it read.
@@ -320,6 +362,22 @@ __device__ __forceinline__ float* slice_part(void* ws, int slice, int N, int K) 
 }
 hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
                                 int ds, hipStream_t stream);
+
+// Register budget shared by the kernels that keep one operand in registers
+// (8 registers per f-step), two units' sums (64) and 32 result registers per
+// class block: depth of the register ring between LDS and the matrix
+// instructions (two per fragment, 64 cycles), a divisor of the unit's steps so
+// that the ring's position is the same in every unit. Up to eight deep, less
+// where the registers are full (a spilled register's reload would wait for
+// every buffer-to-LDS load issued before it).
+constexpr int ring_depth(int nfs, int kb) {
+  const int regs = 8 * nfs + 64 + 32 * kb;
+  for (int d : {8, 7, 6, 5, 4})
+    if (nfs % d == 0 && (d == 4 || regs + 4 * d < 440)) return d;
+  return 4;
+}
+// Most f-steps for each count of class blocks.
+constexpr int max_steps(int kb) { return kb == 1 ? 40 : kb == 2 ? 32 : 20; }
 
 }  // namespace lg
 

@@ -23,35 +23,6 @@ static size_t xreg_ws_bytes(int ds, int64_t N, int64_t K);
 
 namespace {
 
-// LDS byte address of a pointer into the dynamic LDS array.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
-typedef int rsrc_t __attribute__((ext_vector_type(4)));
-
-// 1 KiB from global memory straight into LDS: lane l's 16 bytes at byte offset
-// `off` of the buffer land at lds + 16 l; offsets past the buffer's end
-// deliver zeros. Issued as assembly so that the compiler does not take every
-// later LDS read for one that may overlap it (it would wait for all loads
-// before each read); it writes no register, and the waits are explicit.
-__device__ __forceinline__ void dma_1k(rsrc_t rsrc, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(lds), "v"(off), "s"(rsrc)
-               : "memory");
-}
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)(uintptr_t)p;
-  rsrc_t r;
-  r.x = (int)(uint32_t)a;
-  r.y = (int)(uint32_t)(a >> 32);
-  r.z = (int)bytes;
-  r.w = 0x00020000;
-  return r;
-}
-
 template <class Tr>
 __device__ __forceinline__ uint32_t h_pair(float a, float b) {
   return (Tr::nonneg(a) ? 0x3F80u : 0xBF80u) | (Tr::nonneg(b) ? 0x3F800000u : 0xBF800000u);
@@ -60,17 +31,6 @@ __device__ __forceinline__ uint32_t h_pair(float a, float b) {
 constexpr int kNX = 2;                       // sample tiles of 32 per wave
 constexpr int kXTile = 32 * kNX * kWaves;    // samples per workgroup
 
-// Depth of the register ring between LDS and the matrix instructions (two per
-// fragment, 64 cycles): a divisor of the unit's steps, so that the ring's
-// position is the same in every unit.
-// Up to eight deep, less where the registers are full (a spilled register's
-// reload would wait for every buffer-to-LDS load issued before it).
-constexpr int ring_depth(int nfs, int kb) {
-  const int regs = 8 * nfs + 64 + 32 * kb;  // X, two units' sums, scores
-  for (int d : {8, 7, 6, 5, 4})
-    if (nfs % d == 0 && (d == 4 || regs + 4 * d < 440)) return d;
-  return 4;
-}
 // Fragments per LDS slot: a unit's B steps, its C, whole loads per wave.
 constexpr int unit_frags(int nfs, int kb) { return (nfs + 2 * kb + 3) / 4 * 4; }
 // LDS slots: one being read, one complete, the others in flight.
@@ -133,27 +93,34 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
     const uint32_t row_bytes = (uint32_t)F * Tr::kEsz;
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(xb), 0, (int)(((uint32_t)rows * row_bytes + 3u) & ~3u), 0x00020000);
+    uint32_t after[kNX], sh[kNX];  // the first word past a row's f-steps; bytes to shift
 #pragma unroll
     for (int t = 0; t < kNX; ++t) {
-      const uint32_t b0 = (uint32_t)(32 * (kNX * wave + t) + (lane & 31)) * row_bytes +
-                          (uint32_t)(lane >> 5) * 16u;
-      if (row_bytes % 4 == 0) {
+      const uint32_t b0 = (uint32_t)(32 * (kNX * wave + t) + (lane & 31)) * row_bytes;
+      sh[t] = b0 & 3u;
+      const uint32_t a0 = (b0 & ~3u) + (uint32_t)(lane >> 5) * 16u;
 #pragma unroll
-        for (int s = 0; s < NFS; ++s)
-          xf[s][t] = __builtin_bit_cast(
-              uint4, __builtin_amdgcn_raw_buffer_load_b128(xrs, b0 + 32u * s, 0, 0));
-      } else {
-        const uint32_t a0 = b0 & ~3u, sh = b0 & 3u;
+      for (int s = 0; s < NFS; ++s)
+        xf[s][t] = __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(xrs, a0 + 32u * s, 0, 0));
+      after[t] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xrs, a0 + 32u * NFS, 0, 0);
+    }
+    if (row_bytes % 4 != 0) {
+      // rows that start inside a dword: the word after a lane's features is
+      // the first one of the other half of the wave, of this f-step (lower
+      // half) or of the next one
+#pragma unroll
+      for (int t = 0; t < kNX; ++t) {
+        uint32_t o = swap_halves(xf[0][t].x);
 #pragma unroll
         for (int s = 0; s < NFS; ++s) {
-          const uint4 w = __builtin_bit_cast(
-              uint4, __builtin_amdgcn_raw_buffer_load_b128(xrs, a0 + 32u * s, 0, 0));
-          const uint32_t w4 =
-              (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xrs, a0 + 32u * s + 16u, 0, 0);
-          xf[s][t] = make_uint4(__builtin_amdgcn_alignbyte(w.y, w.x, sh),
-                                __builtin_amdgcn_alignbyte(w.z, w.y, sh),
-                                __builtin_amdgcn_alignbyte(w.w, w.z, sh),
-                                __builtin_amdgcn_alignbyte(w4, w.w, sh));
+          const uint32_t on = swap_halves(s + 1 < NFS ? xf[s + 1 < NFS ? s + 1 : s][t].x : after[t]);
+          const uint4 v = xf[s][t];
+          xf[s][t] = make_uint4(__builtin_amdgcn_alignbyte(v.y, v.x, sh[t]),
+                                __builtin_amdgcn_alignbyte(v.z, v.y, sh[t]),
+                                __builtin_amdgcn_alignbyte(v.w, v.z, sh[t]),
+                                __builtin_amdgcn_alignbyte((lane >> 5) ? on : o, v.w, sh[t]));
+          o = on;
         }
       }
     }
@@ -349,10 +316,7 @@ hipError_t launch_xreg_t(const XregArgs& a, int64_t N, int ds) {
   return hipGetLastError();
 }
 
-// Instances: unit steps in fours up to 40 for one class block, fewer where the
-// score accumulators of more class blocks take the registers.
-constexpr int max_steps(int kb) { return kb == 1 ? 40 : kb == 2 ? 32 : 20; }
-
+// Instances: unit steps in fours up to max_steps.
 template <class Tr, int KB, int NFS = 8>
 hipError_t launch_xreg_steps(int steps, const XregArgs& a, int64_t N, int ds) {
   if constexpr (NFS <= max_steps(KB)) {
