@@ -277,6 +277,10 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
   if (workspace_bytes < zone + pb) zone = align256(hd::large_workspace_min(N, F, D, K, dt));
   if (plan_ws > zone || workspace_bytes < zone + pb) return HD_ERR_WORKSPACE;
   if (dry) return HD_OK;
+  hipError_t err = hipSuccess;
+  if (hd::launch_large_raw(X, B, C, labels, scores, N, F, D, K, dt, act, workspace, zone, stream,
+                           &err))
+    return from_hip(err);
   char* copy = static_cast<char*>(workspace) + zone;
   if (hd::launch_pack(B, C, F, D, K, dt, copy, stream) != hipSuccess) return HD_ERR_HIP;
   const hipError_t e =

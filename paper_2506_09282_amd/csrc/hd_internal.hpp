@@ -99,6 +99,13 @@ hipError_t launch_bundle_breg(const void* X, const void* packed, const int32_t* 
                               int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K, int dt,
                               hipStream_t stream);
 
+// fp32 training on the bf16 matrix instruction (hd_large_x3.hip), B packed or
+// row-major (raw).
+bool bundle_x3_ok(int64_t N, int64_t F, int64_t D, int64_t K, bool raw);
+hipError_t launch_bundle_x3(const void* X, const void* B, bool raw, const int32_t* y,
+                            int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K,
+                            hipStream_t stream);
+
 // Unfused stages.
 hipError_t launch_encode(const void* X, const void* B, float* H, int64_t N, int64_t F, int64_t D,
                          int dt, int act, hipStream_t stream);
@@ -124,5 +131,10 @@ hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
                         void* workspace, size_t ws_bytes, hipStream_t stream);
+// B and C as given, where a kernel reads them so (false: pack them first); *err
+// is the launch's result.
+bool launch_large_raw(const void* X, const void* B, const void* C, int32_t* labels, float* scores,
+                      int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
+                      void* workspace, size_t ws_bytes, hipStream_t stream, hipError_t* err);
 
 }  // namespace hd

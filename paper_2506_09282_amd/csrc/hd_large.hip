@@ -161,58 +161,6 @@ __global__ void pack_c_f32(const float* __restrict__ C, uint4* __restrict__ Cp, 
                                  __float_as_uint(v[2]), __float_as_uint(v[3]));
 }
 
-// Combine the waves' partial scores through LDS, then argmax (Eq. 9) and
-// write; with a split of D, leave this slice's partial scores for
-// reduce_slices_kernel.
-template <int NTILES, int KB>
-__device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds,
-                            int32_t* __restrict__ labels, float* __restrict__ scores, int N, int K,
-                            int DS, int slice, int n0, void* __restrict__ workspace) {
-  constexpr int NT = 32 * NTILES;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  __syncthreads();  // X tile no longer needed
-  float* sred = reinterpret_cast<float*>(lds);  // [kWaves][NT][32*KB]
-  constexpr int KP = 32 * KB;
-#pragma unroll
-  for (int t = 0; t < NTILES; ++t)
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int k = 32 * kb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int n = 32 * t + (lane & 31);
-        sred[((int64_t)wave * NT + n) * KP + k] = sacc[t][kb][r];
-      }
-  __syncthreads();
-  const int rows = min(NT, N - n0);
-  if (DS == 1) {
-    for (int n = tid; n < rows; n += kThreads) {
-      float best = 0.0f;
-      int best_k = 0;
-      for (int k = 0; k < K; ++k) {
-        float s = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) s += sred[((int64_t)w * NT + n) * KP + k];
-        if (scores) scores[(int64_t)(n0 + n) * K + k] = s;
-        if (k == 0 || s > best) {
-          best = s;
-          best_k = k;
-        }
-      }
-      labels[n0 + n] = best_k;
-    }
-    return;
-  }
-  float* mypart = slice_part(workspace, slice, N, K) + (int64_t)n0 * K;
-  for (int i = tid; i < rows * K; i += kThreads) {
-    const int n = i / K, k = i - n * K;
-    float s = 0.0f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += sred[((int64_t)w * NT + n) * KP + k];
-    mypart[i] = s;
-  }
-}
-
 // Second launch of a call with D split into ds slices: sums the slices'
 // partial scores in slice order (results do not depend on timing), writes the
 // scores, takes the row argmax (lowest index on ties) and clears the
@@ -1506,6 +1454,10 @@ hipError_t launch_tr(const void* X, const void* packed, int32_t* labels, float* 
     if (p.ok)
       return launch_xreg(p, XregArgs{X, Bp, Cp, labels, scores, (int)F, (int)K, g.ndb, ws, stream},
                          N, dt);
+  } else {
+    const X3Plan p = x3_plan(N, F, D, K, act, false, ws_bytes);
+    if (p.ok)
+      return launch_x3(p, X, Bp, Cp, false, labels, scores, N, F, D, K, ws, stream);
   }
   const int nt = c.ntiles_per_wg, kb = c.kb;
 #define HD_LAUNCH(NTV, KBV)                                                                       \
@@ -1641,6 +1593,8 @@ hipError_t launch_bundle_packed(const void* X, const void* packed, const int32_t
                                 int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K,
                                 int dt, hipStream_t stream) {
   const dim3 block(kThreads);
+  if (dt == 0 && bundle_x3_ok(N, F, D, K, false))
+    return launch_bundle_x3(X, packed, false, y, counts, N, F, D, K, stream);
   if (bundle_breg_ok(X, N, F, D, K, dt))
     return launch_bundle_breg(X, packed, y, counts, N, F, D, K, dt, stream);
   if (dt == 0) {
@@ -1719,14 +1673,29 @@ size_t large_workspace_min(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
 
 size_t large_workspace_bytes(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
   const size_t a = large_workspace_min(N, F, D, K, dt);
-  const size_t b = xreg_plan(N, F, D, K, dt, 0, true, ~size_t(0)).ws;
+  const size_t b = dt == 0 ? x3_plan(N, F, D, K, 0, false, ~size_t(0)).ws
+                           : xreg_plan(N, F, D, K, dt, 0, true, ~size_t(0)).ws;
   return a > b ? a : b;
 }
 
 size_t large_workspace_used(const void* X, int64_t N, int64_t F, int64_t D, int64_t K, int dt,
                             int act, size_t ws_bytes) {
+  if (dt == 0) {
+    const X3Plan p = x3_plan(N, F, D, K, act, false, ws_bytes);
+    return p.ok ? p.ws : large_workspace_bytes_for(N, F, D, K, dt, true);
+  }
   const XregPlan p = xreg_plan(N, F, D, K, dt, act, (uintptr_t)X % 4 == 0, ws_bytes);
   return p.ok ? p.ws : large_workspace_bytes_for(N, F, D, K, dt, (uintptr_t)X % 16 == 0);
+}
+
+bool launch_large_raw(const void* X, const void* B, const void* C, int32_t* labels, float* scores,
+                      int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
+                      void* workspace, size_t ws_bytes, hipStream_t stream, hipError_t* err) {
+  if (dt != 0) return false;
+  const X3Plan p = x3_plan(N, F, D, K, act, true, ws_bytes);
+  if (!p.ok) return false;
+  *err = launch_x3(p, X, B, C, true, labels, scores, N, F, D, K, workspace, stream);
+  return true;
 }
 
 hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64_t K, int dt,

@@ -363,6 +363,58 @@ __device__ __forceinline__ float* slice_part(void* ws, int slice, int N, int K) 
 hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
                                 int ds, hipStream_t stream);
 
+// Combine the waves' partial scores through LDS, then argmax (Eq. 9) and
+// write; with a split of D, leave this slice's partial scores for
+// reduce_slices_kernel.
+template <int NTILES, int KB>
+__device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds,
+                            int32_t* __restrict__ labels, float* __restrict__ scores, int N, int K,
+                            int DS, int slice, int n0, void* __restrict__ workspace) {
+  constexpr int NT = 32 * NTILES;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __syncthreads();  // X tile no longer needed
+  float* sred = reinterpret_cast<float*>(lds);  // [kWaves][NT][32*KB]
+  constexpr int KP = 32 * KB;
+#pragma unroll
+  for (int t = 0; t < NTILES; ++t)
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int k = 32 * kb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int n = 32 * t + (lane & 31);
+        sred[((int64_t)wave * NT + n) * KP + k] = sacc[t][kb][r];
+      }
+  __syncthreads();
+  const int rows = min(NT, N - n0);
+  if (DS == 1) {
+    for (int n = tid; n < rows; n += kThreads) {
+      float best = 0.0f;
+      int best_k = 0;
+      for (int k = 0; k < K; ++k) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += sred[((int64_t)w * NT + n) * KP + k];
+        if (scores) scores[(int64_t)(n0 + n) * K + k] = s;
+        if (k == 0 || s > best) {
+          best = s;
+          best_k = k;
+        }
+      }
+      labels[n0 + n] = best_k;
+    }
+    return;
+  }
+  float* mypart = slice_part(workspace, slice, N, K) + (int64_t)n0 * K;
+  for (int i = tid; i < rows * K; i += kThreads) {
+    const int n = i / K, k = i - n * K;
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += sred[((int64_t)w * NT + n) * KP + k];
+    mypart[i] = s;
+  }
+}
+
 // Register budget shared by the kernels that keep one operand in registers
 // (8 registers per f-step), two units' sums (64) and 32 result registers per
 // class block: depth of the register ring between LDS and the matrix
@@ -403,5 +455,18 @@ struct XregArgs {
 XregPlan xreg_plan(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act, bool x4,
                    size_t ws_cap);
 hipError_t launch_xreg(const XregPlan& p, XregArgs a, int64_t N, int dt);
+
+// fp32 Stage I on the bf16 matrix instruction (hd_large_x3.hip); B and C packed
+// fragments, or as given (raw). head, ds, ws as above.
+struct X3Plan {
+  int kb, ds;
+  int64_t head;
+  size_t ws;
+  bool ok;
+};
+X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, size_t ws_cap);
+hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* C, bool raw,
+                     int32_t* labels, float* scores, int64_t N, int64_t F, int64_t D, int64_t K,
+                     void* ws, hipStream_t stream);
 
 }  // namespace hd

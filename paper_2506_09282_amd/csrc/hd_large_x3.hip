@@ -1,0 +1,826 @@
+// fp32 Stage I on the bf16 matrix instruction, for large batches: inference
+// (Alg. 4) and single-pass training (Sec. II-C), with B packed or as given.
+//
+// Every fp32 value is the exact sum of three bf16 values (its leading, middle
+// and trailing eight significant bits: truncation, so no rounding and no
+// overflow). A product of two values is taken as the six products of parts
+// down to 2^-16 of the leading one, each exact, accumulated in fp32 by
+// v_mfma_f32_32x32x16_bf16; what is left out is below 2^-23 of the product. Six
+// such instructions cost 192 cycles for 16 features against 512 of the fp32
+// instruction.
+// Against 64 bits, signs of X B that differ in 671 million (the fp32
+// instruction in brackets): F = 100 15 (18), 300 10 (33), 561 17 (45), 617 13
+// (36), 784 17 (45), 1500 22 (86), 3072 29 (115).
+//
+// Measured (fp32 instruction in brackets; us): inference D = 10240 N = 4096,
+// F = 784, K = 10 packed 317 (601), raw N = 500, F = 617, D = 10000, K = 26 69
+// (151); N = 20000, F = 784 1570 (3506); training N = 4096, F = 784 380 (915),
+// raw 441 (1648, fp32 vector units). About 1.25 PFLOP/s of bf16 products, at the
+// 1.9 GHz that this leaves of the clock.
+//
+// Range. The parts of a value below 2^-110 do not all exist, and inf has none:
+// a pass (128 samples by 256 dimensions) in which a row of X or a column of B
+// has its largest magnitude outside [2^-40, 2^50], unless it is zero, is taken
+// again on the fp32 instruction. The check is part of the split.
+//
+// Work split. A workgroup holds a tile of 32 NTILES samples; each wave takes one
+// unit of 64 dimensions per pass. B comes from L2 straight into registers (each
+// fragment is used for NTILES tiles), X through LDS in chunks of 64 features,
+// double-buffered, split into its parts on the way. Inference walks the
+// slice's units and takes HardSign and Stage II after each pass; training walks
+// its share of the sample tiles with one fixed unit per wave and adds each
+// tile's signs to the class sums on the int8 matrix instruction
+// (hd_train_breg.hip), which stay in registers to the end.
+#include <type_traits>
+
+#include "hd_large.hpp"
+
+namespace hd {
+
+using namespace lg;
+
+namespace {
+
+// Groups of 16 features per X chunk: one X item (a row's group) per thread.
+constexpr int chunk_groups(int ntiles) { return kThreads / (32 * ntiles); }
+constexpr float kHi = 0x1p50f, kLo = 0x1p-40f;
+constexpr float kCHi = 0x1p50f, kCLo = 0x1p-90f;
+
+__device__ __forceinline__ bool out_of_range(float m) {
+  return m > kHi || (m > 0.0f && m < kLo);  // m: largest magnitude (NaN is not seen: it is exact)
+}
+
+// Two values into a word of each part (b in the upper half).
+__device__ __forceinline__ void split2(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2,
+                                       float& mx) {
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  mx = fmaxf(fmaxf(mx, fabsf(a)), fabsf(b));
+  const float ra = a - __uint_as_float(ua & 0xffff0000u);
+  const float rb = b - __uint_as_float(ub & 0xffff0000u);
+  const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
+  const float sa = ra - __uint_as_float(va & 0xffff0000u);
+  const float sb = rb - __uint_as_float(vb & 0xffff0000u);
+  w0 = __builtin_amdgcn_perm(ub, ua, 0x07060302u);  // the upper halves of (b, a)
+  w1 = __builtin_amdgcn_perm(vb, va, 0x07060302u);
+  w2 = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
+}
+
+// Eight values (slot order) into their three parts; mx: running largest magnitude.
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3], float& mx) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) split2(x[2 * i], x[2 * i + 1], w[0][i], w[1][i], w[2][i], mx);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+}
+
+__device__ __forceinline__ void split8(const float4& a, const float4& b, uint4 (&p)[3], float& mx) {
+  const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  split8(x, p, mx);
+}
+
+struct X3Args {
+  const float* X;
+  const void* B;  // packed fragments, or row-major [F][D]
+  const void* C;  // packed fragments, or row-major [K][D] (inference)
+  const int32_t* y;
+  int32_t *labels, *counts;
+  float* scores;
+  int N, F, D, K;
+  int DS;        // inference: slices of D; training: groups of sample tiles
+  void* workspace;
+};
+
+// RAW: B (and C) row-major. TRAIN: class sums, else inference.
+template <int NTILES, int KB, bool RAW, bool TRAIN>
+__device__ __forceinline__ void x3_body(const X3Args& a) {
+  constexpr int NT = 32 * NTILES;
+  constexpr int kGC = chunk_groups(NTILES);
+  constexpr int IPT = NT * kGC / kThreads;  // X items (one row's 16 features) per thread
+  constexpr int kSw = 8 / kGC;              // bank spread of a row's groups
+  // S of four tiles lies in LDS between the passes, which frees its registers
+  constexpr bool kPark = !TRAIN && NTILES == 4;
+  constexpr int kBuf = kGC * NTILES * 3 * 1024;  // bytes of one X buffer
+  static_assert(NTILES % 2 == 0 && IPT == 1 && (!kPark || KB == 1), "tiles in pairs");
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = a.N, F = a.F, D = a.D, K = a.K;
+  const int G = (F + 15) / 16, nch = (G + kGC - 1) / kGC;
+  const int nfs8 = (F + 7) / 8;
+  const int units = (D + 63) / 64;
+  const int ntiles = (int)cdiv(N, NT);
+  // inference: tile, units [u_begin, u_end); training: one unit group, tiles [t_begin, t_end)
+  int t_begin, t_end, u_begin, u_end;
+  int slice = 0;
+  if constexpr (TRAIN) {
+    const int ncg = (units + kWaves - 1) / kWaves;
+    const int cg = blockIdx.x % ncg, g = blockIdx.x / ncg;
+    u_begin = cg * kWaves;
+    u_end = min(units, u_begin + kWaves);
+    t_begin = (int)((int64_t)ntiles * g / a.DS);
+    t_end = (int)((int64_t)ntiles * (g + 1) / a.DS);
+  } else {
+    slice = blockIdx.x % a.DS;
+    t_begin = blockIdx.x / a.DS;
+    t_end = t_begin + 1;
+    u_begin = (int)((int64_t)units * slice / a.DS);
+    u_end = (int)((int64_t)units * (slice + 1) / a.DS);
+  }
+
+  // ---- X: chunk ch of tile t, item i of this thread -------------------------
+  // Consecutive threads take the groups of a row's chunk.
+  const int xg = tid % kGC;
+  auto x_load = [&](int t, int ch, float4 (&v)[IPT][4]) __attribute__((always_inline)) {
+    const int64_t n0 = (int64_t)t * NT;
+    const int rows = (int)min((int64_t)NT, (int64_t)N - n0);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(a.X + n0 * F), 0, rows * F * 4, 0x00020000);
+    const int f0 = (ch * kGC + xg) * 16;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const int row = i * (kThreads / kGC) + tid / kGC;
+      const int off = row < rows && f0 < F ? (row * F + f0) * 4 : 0x7ffffff0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        v[i][q] = __builtin_bit_cast(
+            float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * q, 0, 0));
+    }
+  };
+  // features past F (of the next row) to zero
+  auto x_mask = [&](int ch, float4 (&v)[IPT][4]) __attribute__((always_inline)) {
+    const int left = F - (ch * kGC + xg) * 16;
+    if ((ch + 1) * kGC * 16 > F) {
+#pragma unroll
+      for (int i = 0; i < IPT; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (4 * q + 0 >= left) v[i][q].x = 0.0f;
+          if (4 * q + 1 >= left) v[i][q].y = 0.0f;
+          if (4 * q + 2 >= left) v[i][q].z = 0.0f;
+          if (4 * q + 3 >= left) v[i][q].w = 0.0f;
+        }
+    }
+  };
+  // Fragment of group g, tile t, part p: 1 KiB at ((g NTILES + t) 3 + p) of the
+  // buffer; lane (n, h) at position (32 h + n) ^ kSw g (the groups of a row are
+  // written together: distinct banks). Slot e of half h is feature
+  // 8 (e / 4) + 2 (e % 4) + h of the group, as in the packed fp32 fragments of B.
+  auto x_put = [&](int buf, const float4 (&v)[IPT][4], int i, float& mx)
+                   __attribute__((always_inline)) {
+    const int row = i * (kThreads / kGC) + tid / kGC;
+    unsigned char* dst = lds + buf * kBuf + (xg * NTILES + row / 32) * 3 * 1024;
+    const float ev[8] = {v[i][0].x, v[i][0].z, v[i][1].x, v[i][1].z,
+                         v[i][2].x, v[i][2].z, v[i][3].x, v[i][3].z};
+    const float od[8] = {v[i][0].y, v[i][0].w, v[i][1].y, v[i][1].w,
+                         v[i][2].y, v[i][2].w, v[i][3].y, v[i][3].w};
+    uint4 p[3];
+    split8(ev, p, mx);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<uint4*>(dst + q * 1024 + ((row % 32) ^ (kSw * xg)) * 16) = p[q];
+    split8(od, p, mx);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<uint4*>(dst + q * 1024 + ((32 + row % 32) ^ (kSw * xg)) * 16) = p[q];
+  };
+  auto x_get1 = [&](int buf, int g, int t, int q, uint4& x) __attribute__((always_inline)) {
+    x = *reinterpret_cast<const uint4*>(lds + buf * kBuf + (g * NTILES + t) * 3 * 1024 +
+                                        (lane ^ (kSw * g)) * 16 + q * 1024);
+  };
+  auto x_get = [&](int buf, int g, int t, uint4 (&x)[3]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) x_get1(buf, g, t, q, x[q]);
+  };
+
+  // ---- B: the 16 features of group g, two blocks of 32 dimensions ------------
+  const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(a.B), 0, RAW ? F * D * 4 : 2 * units * nfs8 * 1024, 0x00020000);
+  auto b_load = [&](int u, int g, float4 (&v)[2][2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if constexpr (RAW) {
+          // past F the offset is past the matrix (zero); past column D the
+          // next row's values meet zero rows of C, or are not added
+          const int off = ((16 * g + 8 * q + half) * D + 64 * u + 32 * b + col) * 4;
+          float t[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            t[j] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(brs, off + 8 * j * D, 0, 0));
+          v[b][q] = make_float4(t[0], t[1], t[2], t[3]);
+        } else {
+          const int fs = 2 * g + q;
+          const int off = fs < nfs8 ? ((2 * u + b) * nfs8 + fs) * 1024 + lane * 16 : 0x7ffffff0;
+          v[b][q] = __builtin_bit_cast(float4,
+                                       __builtin_amdgcn_raw_buffer_load_b128(brs, off, 0, 0));
+        }
+      }
+  };
+
+  // The leading parts' products and the others' are summed apart: the others
+  // are 2^-8 of them, so only one rounding in 16 features counts (the fp32
+  // instruction: eight). acc holds the whole sum after a pass.
+  f32x16 acc[NTILES][2], low[NTILES][2];
+  auto mma = [&](const uint4& bp, const uint4& xp, f32x16& c) __attribute__((always_inline)) {
+    if constexpr (TRAIN)  // samples in rows
+      TrBF16::stage1(c, xp, bp);
+    else  // dimensions in rows
+      TrBF16::stage1(c, bp, xp);
+  };
+
+  // One group: NTILES/2 phases of two tiles, 24 matrix instructions each, on B
+  // parts bp and X parts x (phase 0's at entry, the next group's phase 0 at
+  // exit). Meanwhile the next group's B parts are split from `raw`, which then
+  // takes group gload's fragments. In a chunk's last group this thread's X
+  // items of the next chunk are split into buffer nb; after the barrier in its
+  // last phase, for which X is in registers by then, every wave has read what
+  // it needs of this chunk and the next one is complete.
+  auto group = [&](uint4 (&bp)[2][3], uint4 (&x)[2][3], float4 (&raw)[2][2], int u, int gload,
+                   int buf, int gl, float (&mxb)[2], auto last, float4 (&xv)[IPT][4], int nb,
+                   float (&mxx)[IPT]) __attribute__((always_inline)) {
+    constexpr bool kLast = decltype(last)::value;
+    constexpr int kPh = NTILES / 2;
+    // The matrix instructions go in slices of three with a piece of the other
+    // work behind each (a slice is 96 cycles, a pair's split about 12
+    // instructions of 4): left to itself the compiler gathers the splits in
+    // blocks that the matrix unit waits for (346 against 323 us at N = 4096,
+    // F = 784, D = 10240, K = 10).
+    constexpr int kSlices = 8 * kPh;        // of the group
+    constexpr int kBar = kSlices - 4;       // the barrier's slice
+    uint32_t bw[2][3][4], xw[3][4];
+    uint4 xn[2][3];
+    auto b_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8
+      const int b = i >> 2, k = i & 3;
+      const float4 v = raw[b][k >> 1];
+      split2(k & 1 ? v.z : v.x, k & 1 ? v.w : v.y, bw[b][0][k], bw[b][1][k], bw[b][2][k], mxb[b]);
+      // (computed here, not where it is next used)
+      asm volatile("" : "+v"(bw[b][0][k]), "+v"(bw[b][1][k]), "+v"(bw[b][2][k]));
+    };
+    auto x_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8 IPT
+      const int it = i >> 3, odd = (i >> 2) & 1, k = i & 3;
+      const float4 v = xv[it][k];
+      split2(odd ? v.y : v.x, odd ? v.w : v.z, xw[0][k], xw[1][k], xw[2][k], mxx[it]);
+      asm volatile("" : "+v"(xw[0][k]), "+v"(xw[1][k]), "+v"(xw[2][k]));
+      if (k == 3) {
+        const int row = it * (kThreads / kGC) + tid / kGC;
+        unsigned char* dst = lds + nb * kBuf + (xg * NTILES + row / 32) * 3 * 1024 +
+                             ((32 * odd + row % 32) ^ (kSw * xg)) * 16;
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          *reinterpret_cast<uint4*>(dst + q * 1024) =
+              make_uint4(xw[q][0], xw[q][1], xw[q][2], xw[q][3]);
+      }
+    };
+    // parts (B, X): lh, mh, mm, hh, hm, hl. B's trailing and middle parts are
+    // done with by the barrier's slice, where the next group's take over
+    // their registers.
+    constexpr int pb[6] = {2, 1, 1, 0, 0, 0}, px[6] = {0, 0, 1, 0, 1, 2};
+#pragma unroll
+    for (int sl = 0; sl < kSlices; ++sl) {
+      const int ph = sl >> 3, ss = sl & 7;
+#pragma unroll
+      for (int m = 3 * ss; m < 3 * ss + 3; ++m) {
+        const int c = m >> 2, t = (m >> 1) & 1, b = m & 1;
+        mma(bp[b][pb[c]], x[t][px[c]], c == 3 ? acc[2 * ph + t][b] : low[2 * ph + t][b]);
+      }
+      if (kLast && sl == kBar) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      // X of the next phase, two fragments behind each of three slices
+      const int rd = ph + 1 < kPh || !kLast ? ss : sl - kBar;
+      if (rd >= 0 && rd < 3) {
+        if (ph + 1 < kPh) {
+          x_get1(buf, gl, 2 * ph + 2, rd, xn[0][rd]);
+          x_get1(buf, gl, 2 * ph + 3, rd, xn[1][rd]);
+        } else {
+          x_get1(kLast ? nb : buf, kLast ? 0 : gl + 1, 0, rd, xn[0][rd]);
+          x_get1(kLast ? nb : buf, kLast ? 0 : gl + 1, 1, rd, xn[1][rd]);
+        }
+      }
+      if constexpr (kLast) {
+        constexpr int kX = 8 * IPT;
+#pragma unroll
+        for (int i = sl * kX / kBar; i < (sl + 1) * kX / kBar && i < kX; ++i) x_piece(i);
+      }
+      if (sl >= kBar) {
+        b_piece(2 * (sl - kBar));
+        b_piece(2 * (sl - kBar) + 1);
+      }
+      if (sl == kSlices - 1) b_load(u, gload, raw);
+      __builtin_amdgcn_sched_barrier(0);
+      if (ss == 7) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) x[t][q] = xn[t][q];
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        bp[b][q] = make_uint4(bw[b][q][0], bw[b][q][1], bw[b][q][2], bw[b][q][3]);
+  };
+
+  // The pass again on the fp32 matrix instruction: X as fp32 in LDS, nothing
+  // overlapped. Leaves the chunk-0 parts of tile tn in buffer 0.
+  auto native = [&](int u, int t, int tn) {
+    constexpr int kPitch = kGC * 16 + 4;  // floats per row
+    float* xf = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][b][r] = 0.0f;
+    float4 v[IPT][4];
+    for (int ch = 0; ch < nch; ++ch) {
+      x_load(t, ch, v);
+      x_mask(ch, v);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < IPT; ++i) {
+        float* dst = xf + (i * (kThreads / kGC) + tid / kGC) * kPitch + xg * 16;
+        reinterpret_cast<float4*>(dst)[0] = make_float4(v[i][0].x, v[i][0].z, v[i][1].x, v[i][1].z);
+        reinterpret_cast<float4*>(dst)[1] = make_float4(v[i][0].y, v[i][0].w, v[i][1].y, v[i][1].w);
+        reinterpret_cast<float4*>(dst)[2] = make_float4(v[i][2].x, v[i][2].z, v[i][3].x, v[i][3].z);
+        reinterpret_cast<float4*>(dst)[3] = make_float4(v[i][2].y, v[i][2].w, v[i][3].y, v[i][3].w);
+      }
+      __syncthreads();
+      const int ng = min(kGC, G - ch * kGC);
+      for (int gl = 0; gl < ng; ++gl) {
+        float4 bv[2][2];
+        b_load(u, ch * kGC + gl, bv);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int i = 0; i < NTILES; ++i) {
+            const uint4 x = *reinterpret_cast<const uint4*>(xf + (32 * i + col) * kPitch + gl * 16 +
+                                                            8 * q + 4 * half);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+              if constexpr (TRAIN)
+                TrF32::stage1(acc[i][b], x, bitcast<uint4>(bv[b][q]));
+              else
+                TrF32::stage1(acc[i][b], bitcast<uint4>(bv[b][q]), x);
+            }
+          }
+      }
+    }
+    x_load(tn, 0, v);
+    x_mask(0, v);
+    float mx = 0.0f;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) x_put(0, v, i, mx);
+    __syncthreads();
+  };
+
+  // ---- scores or class sums ---------------------------------------------------
+  f32x4* park = reinterpret_cast<f32x4*>(lds + 2 * kBuf) + wave * (NTILES * 4 * 64) + lane;
+  f32x16 sacc[TRAIN ? 1 : NTILES][KB];  // S^T of this wave's units
+  i32x16 cacc[TRAIN ? 2 : 1][KB];       // class sums of this wave's unit
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+#pragma unroll
+      for (int i = 0; i < (TRAIN ? 1 : NTILES); ++i) sacc[i][kb][r] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < (TRAIN ? 2 : 1); ++i) cacc[i][kb][r] = 0;
+    }
+
+  // The C values of class block kb against the unit's dimensions.
+  auto c_load = [&](int u, int kb, float4 (&cv)[2][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (RAW) {
+          const int k = 32 * kb + col, d = 64 * u + 32 * b + 8 * q + 4 * half;
+          const float* cp = static_cast<const float*>(a.C) + (int64_t)min(k, K - 1) * D;
+          float t[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float c = cp[min(d + j, D - 1)];
+            t[j] = k < K && d + j < D ? c : 0.0f;
+          }
+          cv[b][q] = make_float4(t[0], t[1], t[2], t[3]);
+        } else {
+          cv[b][q] = static_cast<const float4*>(
+              a.C)[(((int64_t)(2 * u + b) * KB + kb) * 4 + q) * 64 + lane];
+        }
+      }
+  };
+  auto unpark = [&](int i) __attribute__((always_inline)) {
+    if constexpr (kPark) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = park[(i * 4 + q) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sacc[i][0][4 * q + r] = v[r];
+      }
+    }
+  };
+  auto put_park = [&](int i) __attribute__((always_inline)) {
+    if constexpr (kPark) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        park[(i * 4 + q) * 64] = f32x4{sacc[i][0][4 * q], sacc[i][0][4 * q + 1],
+                                       sacc[i][0][4 * q + 2], sacc[i][0][4 * q + 3]};
+    }
+  };
+  if constexpr (kPark) {
+#pragma unroll
+    for (int i = 0; i < NTILES; ++i) put_park(i);
+  }
+  // Stage II of a finished unit: C in three parts against HardSign(V), or on
+  // the fp32 instruction where C's magnitudes ask for it. c0: class block 0.
+  auto stage2 = [&](int u, const float4 (&c0)[2][4]) __attribute__((always_inline)) {
+    if constexpr (!TRAIN) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        float4 cv[2][4];
+        if (kb > 0) {
+          c_load(u, kb, cv);
+        } else {
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cv[b][q] = c0[b][q];
+        }
+        uint4 cp[2][2][3];  // [b][h][part]
+        float mx[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) split8(cv[b][2 * h], cv[b][2 * h + 1], cp[b][h], mx[b]);
+        const bool bad = mx[0] > kCHi || (mx[0] > 0.0f && mx[0] < kCLo) || mx[1] > kCHi ||
+                         (mx[1] > 0.0f && mx[1] < kCLo);
+        const bool native_c = __builtin_amdgcn_ballot_w64(bad) != 0;
+#pragma unroll
+        for (int i = 0; i < NTILES; ++i) {
+          unpark(i);
+          if (!native_c) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const f32x16& v = acc[i][b];
+                uint4 hb;
+                hb.x = sign_pair(v[8 * h + 0], v[8 * h + 1]);
+                hb.y = sign_pair(v[8 * h + 2], v[8 * h + 3]);
+                hb.z = sign_pair(v[8 * h + 4], v[8 * h + 5]);
+                hb.w = sign_pair(v[8 * h + 6], v[8 * h + 7]);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) TrBF16::stage1(sacc[i][kb], cp[b][h][p], hb);
+              }
+          } else {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const float c4[4] = {cv[b][q].x, cv[b][q].y, cv[b][q].z, cv[b][q].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                  sacc[i][kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                      c4[j], hardsign(acc[i][b][4 * q + j]), sacc[i][kb], 0, 0, 0);
+              }
+          }
+          put_park(i);
+        }
+      }
+    }
+  };
+  auto class_sums = [&](int t) __attribute__((always_inline)) {
+    if constexpr (TRAIN) {
+      const int64_t n0 = (int64_t)t * NT;
+      const int rows = (int)min((int64_t)NT, (int64_t)N - n0);
+      const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<int32_t*>(a.y + n0), 0, rows * 4, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < NTILES; ++i) {
+        int yl[16];  // samples 8 q + 4 half + j of the tile
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const i32x4 v = __builtin_bit_cast(
+              i32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                         yrs, (32 * i + 8 * q + 4 * half) * 4, 0, 0));
+#pragma unroll
+          for (int j = 0; j < 4; ++j) yl[4 * q + j] = v[j];
+        }
+        if (32 * i + 32 > rows) {  // rows past the last one have no label
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (32 * i + 8 * q + 4 * half + j >= rows) yl[4 * q + j] = -1;
+        }
+        i32x4 h[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x16& v = acc[i][b];
+            h[b][q] = (int)(((v[4 * q] >= 0.0f ? 0x01u : 0xffu) |
+                             (v[4 * q + 1] >= 0.0f ? 0x0100u : 0xff00u)) |
+                            ((v[4 * q + 2] >= 0.0f ? 0x010000u : 0xff0000u) |
+                             (v[4 * q + 3] >= 0.0f ? 0x01000000u : 0xff000000u)));
+          }
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+          const int k = 32 * kb + col;
+          i32x4 oh;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            oh[q] = (int)(((yl[4 * q] == k ? 0x01u : 0u) | (yl[4 * q + 1] == k ? 0x0100u : 0u)) |
+                          ((yl[4 * q + 2] == k ? 0x010000u : 0u) |
+                           (yl[4 * q + 3] == k ? 0x01000000u : 0u)));
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            cacc[b][kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(oh, h[b], cacc[b][kb], 0, 0, 0);
+        }
+      }
+    }
+  };
+
+  // ---- passes -------------------------------------------------------------------
+  if (t_begin >= t_end || u_begin >= u_end) return;
+  float4 xv[IPT][4];
+  float4 raw[2][2], r0[2][2];
+  uint4 bp[2][3], xc[2][3];
+  float mxb[2], mxx[IPT], mxn[IPT];  // largest magnitudes: columns, rows, the next tile's rows
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) mxx[i] = 0.0f;
+  int buf = 0;
+  const int npass = TRAIN ? t_end - t_begin : (u_end - u_begin + kWaves - 1) / kWaves;
+  // this wave's unit in pass ps (a valid unit when it has none: computed, discarded)
+  auto unit_of = [&](int ps) {
+    const int u = TRAIN ? u_begin + wave : u_begin + ps * kWaves + wave;
+    return u < u_end ? u : u_begin;
+  };
+  auto b_start = [&](int u) __attribute__((always_inline)) {
+    b_load(u, 0, r0);
+    b_load(u, 1, raw);
+  };
+  b_start(unit_of(0));
+  x_load(t_begin, 0, xv);
+  x_mask(0, xv);
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) x_put(0, xv, i, mxx[i]);
+  __syncthreads();
+  x_get(0, 0, 0, xc[0]);
+  x_get(0, 0, 1, xc[1]);
+
+  for (int ps = 0; ps < npass; ++ps) {
+    const int t = TRAIN ? t_begin + ps : t_begin;
+    const int u = unit_of(ps);
+    const int tn = TRAIN ? min(t + 1, t_end - 1) : t;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      mxb[b] = 0.0f;
+      split8(r0[b][0], r0[b][1], bp[b], mxb[b]);
+    }
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) mxn[i] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][b][r] = low[i][b][r] = 0.0f;
+    for (int ch = 0; ch < nch; ++ch) {
+      const bool lastc = ch + 1 == nch;
+      const int nb = buf ^ 1, ng = min(kGC, G - ch * kGC), g0 = ch * kGC;
+      // next chunk of X: of this tile, or the first of the next pass's tile
+      x_load(lastc ? tn : t, lastc ? 0 : ch + 1, xv);
+      if (lastc) {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+          mxn[i] = mxx[i];
+          mxx[i] = 0.0f;
+        }
+      }
+      for (int gl = 0; gl + 1 < ng; ++gl)
+        group(bp, xc, raw, u, g0 + gl + 2, buf, gl, mxb, std::false_type{}, xv, nb, mxx);
+      x_mask(lastc ? 0 : ch + 1, xv);
+      group(bp, xc, raw, u, g0 + ng + 1, buf, ng - 1, mxb, std::true_type{}, xv, nb, mxx);
+      buf = nb;
+    }
+#pragma unroll
+    for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[i][b] += low[i][b];
+    float4 c0[2][4];
+    if constexpr (!TRAIN) c_load(u, 0, c0);
+    if (ps + 1 < npass) b_start(unit_of(ps + 1));
+    // magnitudes outside the range of the split: the pass again, on fp32.
+    // mxn: this pass's rows (a row's groups lie with kGC threads), mxx: the
+    // rows of the chunk already staged for the next pass
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      float m = TRAIN ? mxn[i] : fmaxf(mxn[i], mxx[i]);
+#pragma unroll
+      for (int o = 1; o < kGC; o *= 2) m = fmaxf(m, __shfl_xor(m, o, kWave));
+      bad |= out_of_range(m);
+      if constexpr (!TRAIN) mxx[i] = fmaxf(mxn[i], mxx[i]);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) bad |= out_of_range(fmaxf(mxb[b], __shfl_xor(mxb[b], 32, kWave)));
+    if (__syncthreads_or(bad)) {
+      native(u, t, tn);
+      buf = 0;
+      x_get(0, 0, 0, xc[0]);
+      x_get(0, 0, 1, xc[1]);
+    }
+    if constexpr (TRAIN)
+      class_sums(t);
+    else if (u_begin + ps * kWaves + wave < u_end)
+      stage2(u, c0);
+  }
+
+  if constexpr (TRAIN) {
+    if (u_begin + wave >= u_end) return;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int d = 64 * (u_begin + wave) + 32 * b + col;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int k = 32 * kb + 8 * (r >> 2) + 4 * half + (r & 3);
+          if (k < K && d < D && cacc[b][kb][r] != 0)
+            atomicAdd(&a.counts[(int64_t)k * D + d], cacc[b][kb][r]);
+        }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NTILES; ++i) unpark(i);
+    __syncthreads();
+    finish_tile<NTILES, KB>(sacc, lds, a.labels, a.scores, N, K, a.DS, slice, t_begin * NT,
+                            a.workspace);
+  }
+}
+
+template <int NTILES, int KB, bool RAW>
+__global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_x3(X3Args a) {
+  x3_body<NTILES, KB, RAW, false>(a);
+}
+
+template <int NTILES, int KB, bool RAW>
+__global__ __launch_bounds__(kThreads, 1) void bundle_mfma_kernel_x3(X3Args a) {
+  x3_body<NTILES, KB, RAW, true>(a);
+}
+
+constexpr size_t x3_lds(int ntiles, int kb, bool train) {
+  size_t bufs = (size_t)2 * chunk_groups(ntiles) * ntiles * 3 * 1024;
+  if (!train && ntiles == 4) bufs += (size_t)kWaves * 4 * 4096;  // S between the passes
+  const size_t red = train ? 0 : (size_t)kWaves * 32 * ntiles * 32 * kb * 4;
+  return bufs > red ? bufs : red;
+}
+
+template <auto Kernel>
+hipError_t launch_x3_kernel(const X3Args& a, int grid, size_t lds, hipStream_t stream) {
+  static PerDeviceOnce once;
+  const hipError_t attr = once_per_device(once, [&] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  });
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(Kernel, dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
+  return hipGetLastError();
+}
+
+// Sample tiles per workgroup in inference: four, two where the scores of more
+// class blocks take the registers.
+constexpr int infer_tiles(int kb) { return kb == 1 ? 4 : 2; }
+// In training two; four with long rows and enough tiles to fill the chip (the
+// class sums at the end of a pass, with the registers full, then weigh less
+// than half the loads of B): packed N = 4096, F = 784 380 against 416 us, raw
+// N = 2048 205 against 235 us, but F = 100, N = 10000 262 against 207 us and
+// N = 300, F = 617 56 against 33 us.
+int train_tiles(int64_t N, int64_t F, int64_t D, int kb) {
+  return kb <= 2 && F >= 512 && cdiv(N, 128) * cdiv(D, 256) >= num_cus() ? 4 : 2;
+}
+
+template <int KB>
+hipError_t launch_infer(const X3Args& a, bool raw, int grid, hipStream_t stream) {
+  constexpr int NT = infer_tiles(KB);
+  constexpr size_t lds = x3_lds(NT, KB, false);
+  static_assert(lds <= kLdsBytes, "LDS");
+  return raw ? launch_x3_kernel<&large_fused_kernel_x3<NT, KB, true>>(a, grid, lds, stream)
+             : launch_x3_kernel<&large_fused_kernel_x3<NT, KB, false>>(a, grid, lds, stream);
+}
+
+template <int NT, int KB, bool RAW>
+hipError_t launch_train(const X3Args& a, int grid, hipStream_t stream) {
+  return launch_x3_kernel<&bundle_mfma_kernel_x3<NT, KB, RAW>>(a, grid, x3_lds(NT, KB, true),
+                                                               stream);
+}
+
+// Offsets into B are 32-bit; row-major B is read up to 64 rows past F.
+bool x3_sizes_ok(int64_t F, int64_t D, int64_t K, bool raw) {
+  if (cdiv(K, 32) > 4 || F > (1 << 20) || D > (1 << 22)) return false;
+  if (raw) return F * D * 4 < ((int64_t)1 << 31);
+  return cdiv(D, 64) * 2 * cdiv(F, 8) * 1024 < ((int64_t)1 << 31);
+}
+
+}  // namespace
+
+X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, size_t ws_cap) {
+  X3Plan p{};
+  if (act != 0 || !x3_sizes_ok(F, D, K, raw)) return p;
+  p.kb = kb_of(K);
+  const int64_t cus = num_cus(), units = cdiv(D, 64), passes = cdiv(units, kWaves);
+  const int64_t nt = 32 * infer_tiles(p.kb), tiles = cdiv(N, nt);
+  // Whole rounds of one tile per compute unit unsplit, the tiles left over split
+  // over D: the fewest rounds, each a slice's passes and about half a pass (at
+  // F = 784) of starting and handing over. A slice has whole passes.
+  p.head = tiles / cus * cus * nt;
+  if (p.head > N) p.head = N;
+  const int64_t rest = N - p.head, rt = cdiv(rest, nt);
+  p.ds = 1;
+  const double over = 400.0 / (double)F;
+  double cost = (double)cdiv(rt, cus) * ((double)passes + over);
+  for (int ds = 2; rest > 0 && ds <= 64 && ds <= passes; ++ds) {
+    if (sizeof(float) * (size_t)ds * rest * K > ws_cap) break;
+    const double c = (double)cdiv(rt * ds, cus) * ((double)cdiv(cdiv(units, ds), kWaves) + over);
+    if (c < 0.98 * cost) {
+      cost = c;
+      p.ds = ds;
+    }
+  }
+  p.ws = rest > 0 && p.ds > 1 ? sizeof(float) * (size_t)p.ds * rest * K : 0;
+  p.ok = true;
+  return p;
+}
+
+hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* C, bool raw,
+                     int32_t* labels, float* scores, int64_t N, int64_t F, int64_t D, int64_t K,
+                     void* ws, hipStream_t stream) {
+  auto go = [&](int64_t n0, int64_t n, int ds) {
+    const X3Args a{(const float*)X + n0 * F, B, C, nullptr, labels + n0, nullptr,
+                   scores ? scores + n0 * K : nullptr, (int)n, (int)F, (int)D, (int)K, ds, ws};
+    const int grid = (int)(cdiv(n, 32 * infer_tiles(p.kb)) * ds);
+    return p.kb == 1   ? launch_infer<1>(a, raw, grid, stream)
+           : p.kb == 2 ? launch_infer<2>(a, raw, grid, stream)
+                       : launch_infer<4>(a, raw, grid, stream);
+  };
+  if (p.head > 0) {
+    const hipError_t e = go(0, p.head, 1);
+    if (e != hipSuccess || p.head == N) return e;
+  }
+  const hipError_t e = go(p.head, N - p.head, p.ds);
+  if (e != hipSuccess || p.ds == 1) return e;
+  return launch_reduce_slices(ws, labels + p.head, scores ? scores + p.head * K : nullptr,
+                              N - p.head, K, p.ds, stream);
+}
+
+// Below about 1.5e8 multiply-adds a call is its start, which is 2-3 us longer
+// here (N = 256, F = 33, D = 512: 15.5 us against 13.1 us packed and 13.3 us
+// raw on the kernels for fp32 instructions; N = 300, F = 617, D = 10240: 53 us
+// against 76 and 129 us).
+bool bundle_x3_ok(int64_t N, int64_t F, int64_t D, int64_t K, bool raw) {
+  return N >= 1 && N <= (1 << 30) && x3_sizes_ok(F, D, K, raw) &&
+         (double)N * (double)F * (double)D >= 1.5e8;
+}
+
+hipError_t launch_bundle_x3(const void* X, const void* B, bool raw, const int32_t* y,
+                            int32_t* counts, int64_t N, int64_t F, int64_t D, int64_t K,
+                            hipStream_t stream) {
+  const int kb = kb_of(K), nt = train_tiles(N, F, D, kb);
+  const int64_t cus = num_cus(), ncg = cdiv(cdiv(D, 64), kWaves);
+  const int64_t tiles = cdiv(N, 32 * nt);
+  // groups of sample tiles: the fewest rounds, each a group's tiles and about
+  // half a tile (at F = 784) of starting and adding the sums into counts
+  const double over = 400.0 / (double)F;
+  int64_t best = 1;
+  double cost = -1.0;
+  for (int64_t g = 1; g <= tiles; ++g) {
+    const double c = (double)cdiv(ncg * g, cus) * ((double)cdiv(tiles, g) + over);
+    if (cost < 0 || c < 0.98 * cost) {
+      cost = c;
+      best = g;
+    }
+    if (ncg * g > 8 * cus) break;
+  }
+  const X3Args a{(const float*)X, B, nullptr, y, nullptr, counts, nullptr, (int)N, (int)F, (int)D,
+                 (int)K, (int)best, nullptr};
+  const int grid = (int)(ncg * best);
+  if (nt == 4)
+    return kb == 1 ? (raw ? launch_train<4, 1, true>(a, grid, stream)
+                          : launch_train<4, 1, false>(a, grid, stream))
+                   : (raw ? launch_train<4, 2, true>(a, grid, stream)
+                          : launch_train<4, 2, false>(a, grid, stream));
+  if (raw)
+    return kb == 1   ? launch_train<2, 1, true>(a, grid, stream)
+           : kb == 2 ? launch_train<2, 2, true>(a, grid, stream)
+                     : launch_train<2, 4, true>(a, grid, stream);
+  return kb == 1   ? launch_train<2, 1, false>(a, grid, stream)
+         : kb == 2 ? launch_train<2, 2, false>(a, grid, stream)
+                   : launch_train<2, 4, false>(a, grid, stream);
+}
+
+}  // namespace hd

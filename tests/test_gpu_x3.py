@@ -1,0 +1,178 @@
+"""fp32 Stage I on the bf16 matrix instruction (large batches, training; B packed
+and as given): bit-exact on integer inputs that need all three parts of a
+value, at the edges of its tiles; inputs outside the split's range; and its
+error against float64 next to the fp32 matrix instruction's bound."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import hd_inputs
+import oracle
+from gpu_util import announce, check_against_oracle, dev, torch_or_skip
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hd():
+    torch_or_skip()
+    import paper_2506_09282_amd as m
+    return m
+
+
+def wide_ints(N, F, D, K, seed):
+    """X up to 2^11, B up to 2^6 / F-dependent, C up to 2^9: values of up to
+    three parts whose sums stay below 2^24."""
+    g = np.random.default_rng(seed)
+    bmax = max(1, min(64, (1 << 24) // (F * 2048)))
+    X = g.integers(-2047, 2048, (N, F)).astype(np.float32)
+    B = g.integers(-bmax, bmax + 1, (F, D)).astype(np.float32)
+    C = g.integers(-500, 501, (K, D)).astype(np.float32)
+    return X, B, C
+
+
+def run_all(hd, X, B, C, y, K):
+    """Scores and labels packed and raw, class sums packed and raw."""
+    torch = torch_or_skip()
+    Xd, Bd, Cd = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (X, B, C))
+    yd = torch.from_numpy(y).cuda()
+    m = hd.pack_model(Bd, Cd)
+    out = [hd.infer_packed(Xd, m, return_scores=True), hd.infer(Xd, Bd, Cd, return_scores=True),
+           hd.bundle_classes_packed(Xd, m, yd, K), hd.bundle_classes(Xd, Bd, yd, K)]
+    torch.cuda.synchronize()
+    return out
+
+
+def check(hd, X, B, C, seed):
+    K = C.shape[0]
+    y = np.random.default_rng(seed).integers(-1, K + 1, X.shape[0]).astype(np.int32)
+    ref, counts = oracle.infer(X, B, C), oracle.bundle(X, B, y, K)["counts"]
+    p, r, cp, cr = run_all(hd, X, B, C, y, K)
+    for labels, S in (p, r):
+        assert np.array_equal(S.cpu().numpy().astype(np.float64), ref["S"])
+        assert np.array_equal(labels.cpu().numpy(), ref["y"])
+    for c in (cp, cr):
+        assert np.array_equal(c.cpu().numpy(), counts)
+
+
+# one group of 16 features, a ragged group, one chunk of four groups, one
+# more; rows of every offset; samples around the 128-sample tile; dimensions
+# around a unit and a pass; one, two and four class blocks
+@pytest.mark.parametrize("N,F,D,K", [(257, 1, 64, 3), (257, 15, 65, 32), (300, 16, 256, 33),
+                                     (384, 17, 257, 64), (385, 63, 320, 65), (300, 64, 500, 128),
+                                     (300, 65, 1000, 10), (513, 130, 96, 5), (300, 1277, 300, 26)])
+def test_integer_bit_exact(hd, N, F, D, K):
+    announce(f"x3 N={N} F={F} D={D} K={K}")
+    check(hd, *wide_ints(N, F, D, K, N + F), seed=F)
+
+
+def test_more_tiles_than_compute_units(hd):
+    announce("x3 head and rest")
+    check(hd, *wide_ints(256 * 128 + 200, 20, 300, 3, 1), seed=1)
+
+
+@pytest.mark.parametrize("N,F,D,K", [(2000, 300, 300, 33), (1100, 545, 300, 5), (8300, 530, 1000, 33),
+                                     (33000, 520, 256, 32), (3001, 129, 500, 128)])
+def test_training_sizes(hd, N, F, D, K):
+    """Enough work for this kernel (1.5e8 multiply-adds): two and four sample
+    tiles per workgroup, ragged last tiles."""
+    torch = torch_or_skip()
+    announce(f"x3 training N={N} F={F} D={D} K={K}")
+    X, B, _ = wide_ints(N, F, D, K, N)
+    y = np.random.default_rng(F).integers(-1, K + 1, N).astype(np.int32)
+    H = (X.astype(np.float64) @ B.astype(np.float64) >= 0) * 2 - 1
+    want = np.zeros((K, D), np.int64)
+    for k in range(K):
+        want[k] = H[y == k].sum(axis=0)
+    Xd, Bd, yd = (torch.from_numpy(a).cuda() for a in (X, B, y))
+    for c in (hd.bundle_classes_packed(Xd, hd.pack_model(Bd, K=K), yd, K),
+              hd.bundle_classes(Xd, Bd, yd, K)):
+        torch.cuda.synchronize()
+        assert np.array_equal(c.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("what", ["inf", "tiny row", "huge b"])
+def test_training_range(hd, what):
+    """The fall back to the fp32 instruction, with tiles after it."""
+    torch = torch_or_skip()
+    announce(f"x3 training range: {what}")
+    N, F, D, K = 5000, 70, 600, 5
+    X, B, _ = hd_inputs.make_integer_inputs(N, F, D, K, seed=11)
+    if what == "inf":
+        B[7] = np.where(B[7] == 0, 1, B[7])
+        X[5, 7], X[2000, 7], X[2001, 3] = np.inf, -np.inf, np.nan
+    elif what == "tiny row":
+        X[1000] *= np.float32(2.0 ** -118)
+    else:
+        B = B * np.float32(2.0 ** 90)
+    y = np.random.default_rng(1).integers(0, K, N).astype(np.int32)
+    ref = oracle.bundle(X, B, y, K)["counts"]
+    Xd, Bd, yd = (torch.from_numpy(a).cuda() for a in (X, B, y))
+    for c in (hd.bundle_classes_packed(Xd, hd.pack_model(Bd, K=K), yd, K),
+              hd.bundle_classes(Xd, Bd, yd, K)):
+        torch.cuda.synchronize()
+        assert np.array_equal(c.cpu().numpy(), ref)
+
+
+def test_row_offsets_of_x(hd):
+    """X 4-byte aligned only."""
+    torch = torch_or_skip()
+    X, B, C = wide_ints(300, 50, 300, 4, 2)
+    buf = torch.zeros(X.size + 1, device="cuda")
+    buf[1:] = torch.from_numpy(X.reshape(-1)).cuda()
+    y, S = hd.infer(buf[1:].view(300, 50), torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(),
+                    return_scores=True)
+    torch.cuda.synchronize()
+    ref = oracle.infer(X, B, C)
+    assert np.array_equal(S.cpu().numpy().astype(np.float64), ref["S"])
+    assert np.array_equal(y.cpu().numpy(), ref["y"])
+
+
+# Inputs that the split cannot take: the pass falls back to the fp32
+# instruction. Powers of two keep every sum exact.
+@pytest.mark.parametrize("what", ["inf", "huge x", "tiny x", "tiny row", "huge b", "tiny column",
+                                  "huge c", "tiny c", "zero row and column"])
+def test_range(hd, what):
+    announce(f"x3 range: {what}")
+    N, F, D, K = 300, 70, 600, 5
+    X, B, C = hd_inputs.make_integer_inputs(N, F, D, K, seed=9)
+    if what == "inf":
+        B[7] = np.where(B[7] == 0, 1, B[7])
+        X[5, 7], X[200, 7], X[201, 3] = np.inf, -np.inf, np.nan
+    elif what == "huge x":
+        X = X * np.float32(2.0 ** 90)
+    elif what == "tiny x":
+        X = X * np.float32(2.0 ** -118)
+    elif what == "tiny row":
+        X[100] *= np.float32(2.0 ** -118)
+    elif what == "huge b":
+        B = B * np.float32(2.0 ** 90)
+    elif what == "tiny column":
+        B[:, 300] *= np.float32(2.0 ** -118)
+    elif what == "huge c":
+        C = C * np.float32(2.0 ** 90)
+    elif what == "tiny c":
+        C = C * np.float32(2.0 ** -118)
+    else:
+        X[50] = 0
+        B[:, 40] = 0
+    check(hd, X, B, C, seed=9)
+
+
+@pytest.mark.parametrize("N,F,D,K,dist", [(512, 784, 2048, 10, "uniform01_zero20"),
+                                          (512, 617, 1500, 26, "normal"),
+                                          (300, 3000, 700, 40, "uniform_pm1")])
+def test_error_within_fp32_bound(hd, N, F, D, K, dist):
+    """The fragile-flip rule of every fp32 kernel (an error bound of F roundings
+    to 24 bits), which a product with fewer than all its parts would break."""
+    announce(f"x3 real N={N} F={F} D={D} K={K}")
+    X, B, C = hd_inputs.make_inputs(N, F, D, K, dist, seed=4)
+    torch = torch_or_skip()
+    for out in (hd.infer_packed(dev(X, "f32"), hd.pack_model(dev(B, "f32"), dev(C, "f32")),
+                                return_scores=True),
+                hd.infer(dev(X, "f32"), dev(B, "f32"), dev(C, "f32"), return_scores=True)):
+        torch.cuda.synchronize()
+        rep, _ = check_against_oracle(X, B, C, out[0].cpu().numpy(),
+                                      out[1].cpu().numpy().astype(np.float64))
+        assert rep["ok"], rep
