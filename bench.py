@@ -238,9 +238,10 @@ def run_stream(args, w):
     ws = torch.zeros(hd.stream_workspace_bytes(nbatch, w.N, w.F, w.D, w.K, torch.float32),
                      dtype=torch.uint8, device=dev)
     stream = torch.cuda.Stream(device=dev)
+    done = torch.zeros(1, dtype=torch.int32, device=dev)  # batch by batch, as a queue's reader sees it
 
     def step():
-        hd.infer_stream(Xd, model, out=(labels, None), workspace=ws)
+        hd.infer_stream(Xd, model, out=(labels, None), workspace=ws, done=done)
 
     with torch.cuda.stream(stream):
         for _ in range(warmup):

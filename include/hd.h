@@ -188,7 +188,10 @@ hd_status hd_infer_packed(const void *X, const void *packed, int32_t *labels, fl
  *   done    NULL or a device/host-mapped counter that is incremented once
  *           per batch whose labels (and scores) have been written.
  *   workspace  hd_infer_stream_workspace_bytes(nbatch, ...) bytes, zeroed
- *           before first use and left zeroed (one region per batch).
+ *           before first use and left zeroed.
+ * With ready and done both NULL nothing shows the batches done one by one, and
+ * a queue long enough runs as one batch of nbatch*N samples on the large-batch
+ * kernels instead (same results up to the order of fp32 sums).
  * Supported: fp32, 1 <= N <= 32, K <= 16, F <= 576, D <= 48 * (compute
  * units - 1); otherwise HD_ERR_UNSUPPORTED (the workspace size query returns
  * 0). The launch holds every compute unit but one with one workgroup each,

@@ -131,6 +131,11 @@ hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
                         void* workspace, size_t ws_bytes, hipStream_t stream);
+// Whether a stream whose batches are all present, and whose batches nobody
+// counts, is faster as one batch on the large-batch kernels (fp32).
+bool stream_as_one_batch(int64_t nbatch, int64_t N, int64_t F, int64_t D, int64_t K, int act,
+                         size_t ws_bytes);
+size_t stream_as_one_ws_bytes(int64_t nbatch, int64_t N, int64_t F, int64_t D, int64_t K);
 // B and C as given, where a kernel reads them so (false: pack them first); *err
 // is the launch's result.
 bool launch_large_raw(const void* X, const void* B, const void* C, int32_t* labels, float* scores,

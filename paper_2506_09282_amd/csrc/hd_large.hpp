@@ -462,6 +462,7 @@ struct X3Plan {
   int kb, ds;
   int64_t head;
   size_t ws;
+  double us;  // about how long the call takes
   bool ok;
 };
 X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, size_t ws_cap);

@@ -753,6 +753,9 @@ X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, si
     }
   }
   p.ws = rest > 0 && p.ds > 1 ? sizeof(float) * (size_t)p.ds * rest * K : 0;
+  const double rounds = (double)(tiles / cus) * (double)passes +
+                        (double)cdiv(rt * p.ds, cus) * (double)cdiv(cdiv(units, p.ds), kWaves);
+  p.us = 14.0 + rounds * (1.05 * (double)cdiv(F, 16) + 5.0);
   p.ok = true;
   return p;
 }

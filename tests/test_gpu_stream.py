@@ -168,3 +168,27 @@ def test_stream_unsupported_shapes_rejected(hd):
     for args in [(4, 33, 561, 10240, 6), (4, 8, 561, 10240, 17), (4, 8, 600, 1024, 6)]:
         assert hd.stream_workspace_bytes(*args, torch.float32) == 0
     assert hd.stream_workspace_bytes(4, 8, 561, 1024, 6, torch.bfloat16) == 0
+
+
+# Queues that are faster as one batch on the large-batch kernels (every batch
+# present, no done counter), next to the same queue batch by batch (done given)
+# on one workspace.
+@pytest.mark.parametrize("nbatch,N,F,D,K", [(300, 1, 561, 10240, 6), (70, 32, 64, 2000, 16),
+                                            (257, 3, 33, 1000, 3), (40, 32, 4, 64, 2)])
+def test_stream_as_one_batch(hd, nbatch, N, F, D, K):
+    torch = torch_or_skip()
+    announce(f"stream as one batch nbatch={nbatch} N={N} F={F} D={D} K={K}")
+    X, B, C = hd_inputs.make_integer_inputs(nbatch * N, F, D, K, seed=nbatch)
+    ref = oracle.infer(X, B, C)
+    model = hd.pack_model(dev(B, "f32"), dev(C, "f32"))
+    X3 = dev(X, "f32").view(nbatch, N, F)
+    full = hd.stream_workspace_bytes(nbatch, N, F, D, K, torch.float32)
+    ws = torch.zeros(full, dtype=torch.uint8, device="cuda")
+    done = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for kw in ({}, {"done": done}, {}):
+        y, S = hd.infer_stream(X3, model, return_scores=True, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        assert np.array_equal(S.cpu().numpy().reshape(-1, K), ref["S"])
+        assert np.array_equal(y.cpu().numpy().reshape(-1), ref["y"])
+        assert int(ws.count_nonzero()) == 0
+    assert int(done.item()) == nbatch
