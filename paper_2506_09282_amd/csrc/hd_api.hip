@@ -75,8 +75,13 @@ Route route(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool tiled) {
   return small_ok ? Route::kSmall : Route::kNone;
 }
 
-// Batch size of each small-path launch for a route.
-int64_t small_n(Route r, int64_t N) { return r == Route::kSmallChunked ? hd::kSmallMaxN : N; }
+// Batch size of each small-path launch for a route, at least (any workspace that
+// served 64-sample launches serves the call) or with room for `most`.
+int64_t small_n(Route r, int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool most) {
+  if (r != Route::kSmallChunked) return N;
+  if (!most || !hd::small_two_pass(F, D, K, dt)) return hd::kSmallMaxN;
+  return N < hd::kSmallTwoPassN ? N : hd::kSmallTwoPassN;
+}
 
 hd_status from_hip(hipError_t e) { return e == hipSuccess ? HD_OK : HD_ERR_HIP; }
 
@@ -177,12 +182,12 @@ static size_t workspace_need(int64_t N, int64_t F, int64_t D, int64_t K, int dt,
   const auto large = query ? hd::large_workspace_bytes : hd::large_workspace_min;
   if ((r == Route::kSmall || r == Route::kSmallChunked) && dt == HD_I8) {
     // an unaligned X takes the large-batch kernels instead
-    const size_t s = hd::small_workspace_bytes(small_n(r, N), F, D, K, dt, det);
+    const size_t s = hd::small_workspace_bytes(small_n(r, N, F, D, K, dt, query), F, D, K, dt, det);
     const size_t l = large(N, F, D, K, dt);
     return s > l ? s : l;
   }
   if (r == Route::kSmall || r == Route::kSmallChunked)
-    return hd::small_workspace_bytes(small_n(r, N), F, D, K, dt, det);
+    return hd::small_workspace_bytes(small_n(r, N, F, D, K, dt, query), F, D, K, dt, det);
   if (packed) return large(N, F, D, K, dt);
   return align256(large(N, F, D, K, dt)) +
          align256(hd::large_packed_bytes(F, D, K, dt));
@@ -245,7 +250,9 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
   if (r == Route::kSmall || r == Route::kSmallChunked) {
     if (dry) return HD_OK;
     if (packed) B = static_cast<const char*>(packed) + image_layout(F, D, K, dt).large;
-    const int64_t step = small_n(r, N);
+    int64_t step = small_n(r, N, F, D, K, dt, packed != nullptr);
+    if (hd::small_workspace_bytes(step, F, D, K, dt, det) > workspace_bytes)
+      step = small_n(r, N, F, D, K, dt, false);
     for (int64_t n0 = 0; n0 < N; n0 += step) {
       const int64_t n = N - n0 < step ? N - n0 : step;
       const hipError_t e = hd::launch_small(
@@ -300,7 +307,7 @@ const char* hd_infer_kernel(int64_t N, int64_t F, int64_t D, int64_t K, hd_dtype
   if (N < 1 || F < 1 || D < 1 || K < 1 || !enums_ok(dt, 0) || !dims_ok(N, F, D, K)) return "";
   const Route r = route(N, F, D, K, dt, packed != 0);
   if (r == Route::kSmall || r == Route::kSmallChunked)
-    return hd::small_kernel_name(small_n(r, N), F, D, K, dt, packed != 0);
+    return hd::small_kernel_name(small_n(r, N, F, D, K, dt, false), F, D, K, dt, packed != 0);
   return r == Route::kLarge ? hd::large_kernel_name(N, F, D, K, dt) : "";
 }
 
@@ -447,11 +454,12 @@ hd_status hd_infer_packed_noalloc(const void* X, const void* packed, int32_t* la
   // (or a caller that wrote the memory) would leave it otherwise: clear the
   // part this call uses with a fill kernel (not a memset node, so the call
   // can be captured in a graph).
-  size_t used = need;
-  if (route(N, F, D, K, dt, true) == Route::kLarge) {
-    const size_t l = hd::large_workspace_used(X, N, F, D, K, dt, act_base(act), kScratchBytes);
-    used = l > used ? l : used;
-  }
+  const Route r = route(N, F, D, K, dt, true);
+  const size_t more =
+      r == Route::kLarge
+          ? hd::large_workspace_used(X, N, F, D, K, dt, act_base(act), kScratchBytes)
+          : hd::small_workspace_bytes(small_n(r, N, F, D, K, dt, true), F, D, K, dt, det_of(act));
+  const size_t used = more > need && more <= kScratchBytes ? more : need;
   if (used > 0 && hd::launch_zero(ws, used, stream) != hipSuccess) return HD_ERR_HIP;
   return infer_common(X, nullptr, nullptr, packed, labels, scores, N, F, D, K, dt, act, ws,
                       kScratchBytes, stream);

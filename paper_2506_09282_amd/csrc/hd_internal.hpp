@@ -38,6 +38,11 @@ int num_cus();
 constexpr int kSmallMaxN = 64;
 constexpr int kSmallReplicas = 32;  // replicated score accumulators
 
+// A packed bf16 or int8 model's fragment kernel takes up to 128 samples in two
+// passes where small_two_pass says so.
+constexpr int kSmallTwoPassN = 128;
+bool small_two_pass(int64_t F, int64_t D, int64_t K, int dt);
+
 bool small_supported(int64_t N, int64_t F, int64_t D, int64_t K, int dt);
 // `act` of launch_small: bit 0 the activation, bit 1 the deterministic reduction.
 constexpr int kSmallActDet = 2;

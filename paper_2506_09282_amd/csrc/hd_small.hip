@@ -101,8 +101,9 @@ SmallPlan plan_small(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int lay
   // int8 runs only on the fragment kernel, for every N
   if (lay == kTiled && x_aligned && (N > 4 || dt == 2) && frag_ms(F) > 0) {
     const int ms = frag_ms(F);
-    int64_t cslots = 1;  // the most blocks any workgroup walks
-    for (int b = 0; b < v.grid; ++b) {
+    // the most blocks any workgroup walks: the first of some XCD's
+    int64_t cslots = 1;
+    for (int b = 0; b < v.grid && b < 8; ++b) {
       const int c = block_walk(b, v.grid, v.nblocks).count();
       cslots = c > cslots ? c : cslots;
     }
@@ -121,10 +122,19 @@ SmallPlan plan_small(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int lay
     // passes of 32
     int64_t nti = cdiv(N, 16), npass = 1;
     int64_t floats = frag_floats(nti);
-    if ((int64_t)sizeof(float) * floats > kLdsBudget && N > 32 && cslots <= 3) {
+    if ((int64_t)sizeof(float) * floats > kLdsBudget && N > 32 && N <= 64 && cslots <= 3) {
       nti = 2;
       npass = 2;
       floats = frag_floats(2);
+    }
+    // 64 < N <= 128 on a bf16 or int8 model: two passes of 64, so that one
+    // call streams B and hands over once (bf16 N = 100, F = 561, D = 10240: two
+    // calls of 64 and 36 took 20.4 us). F >= 16: a pass of one row has a word.
+    if (N > 64) {
+      if (N > kSmallTwoPassN || dt == 0 || cslots > 3 || F < 16) return SmallPlan{};
+      nti = 4;
+      npass = 2;
+      floats = frag_floats(4);
     }
     if (K <= kFragMaxK && (int64_t)sizeof(float) * floats <= kLdsBudget) {
       p.frag = true;
@@ -137,6 +147,7 @@ SmallPlan plan_small(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int lay
       return p;
     }
   }
+  if (N > kSmallMaxN) return SmallPlan{};
   if (N <= 8) {
     p.flat = true;
     p.nb = N <= 1 ? 1 : N <= 2 ? 2 : N <= 4 ? 4 : 8;
@@ -245,7 +256,7 @@ static SmallPlan plan_stream(int64_t N, int64_t F, int64_t D, int64_t K, int dt)
   const int cus = num_cus() > 1 ? num_cus() - 1 : 1;
   p.grid = p.nblocks < cus ? p.nblocks : cus;
   int64_t cslots = 1;
-  for (int b = 0; b < p.grid; ++b) {
+  for (int b = 0; b < p.grid && b < 8; ++b) {  // the first of each XCD walks the most
     const int c = block_walk(b, p.grid, p.nblocks).count();
     cslots = c > cslots ? c : cslots;
   }
@@ -276,6 +287,10 @@ size_t small_workspace_bytes(int64_t N, int64_t F, int64_t D, int64_t K, int dt,
   // every plan's grid is at most one workgroup per column block
   const int64_t slots = det ? cdiv(D, kW) + kGroups : kSmallReplicas;
   return (size_t)kLine * (1 + kGroups) + sizeof(float) * (size_t)slots * N * K;
+}
+
+bool small_two_pass(int64_t F, int64_t D, int64_t K, int dt) {
+  return dt != 0 && plan_small(kSmallTwoPassN, F, D, K, dt, kTiled, true).npass == 2;
 }
 
 bool small_matrix_core(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool tiled) {

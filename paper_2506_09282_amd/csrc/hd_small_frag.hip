@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kFragThreads, 1) void small_frag_mfma_kernel(
     auto x_rows = [&](int pass) { return min(NB, N - NB * pass); };
     // loads of one batch of the pass's words (base: first word index). A
     // pass has at least one word: the first has more than 8 rows of F >= 4,
-    // and a second pass is planned only for rows too long for one pass.
+    // and a second pass is planned only for rows of at least one word.
     auto x_load = [&](XBatch& xb, int pass, int base) {
       const T* Xp = X + (int64_t)NB * pass * F;
       const int nw = x_rows(pass) * F / EPW;
@@ -526,11 +526,14 @@ hipError_t launch_frag_t(const SmallPlan& p, const Args& a, const void* frag) {
 // The ring (reloads inside a loop) only where some workgroup walks more than
 // three blocks; the first workgroup of each XCD walks the most. Two sample
 // passes (planned only without the ring) for 32 < N <= 64 when X of all the
-// samples does not fit LDS.
+// samples does not fit LDS, and for 64 < N <= 128 (bf16, int8).
 template <typename T, int NTI, int MS>
 hipError_t launch_frag(const SmallPlan& p, const Args& a, const void* frag) {
   if constexpr (NTI == 2) {
     if (p.npass == 2) return launch_frag_t<T, 2, MS, false, 2>(p, a, frag);
+  }
+  if constexpr (NTI == 4 && sizeof(T) < 4) {
+    if (p.npass == 2) return launch_frag_t<T, 4, MS, false, 2>(p, a, frag);
   }
   if (p.npass != 1) return hipErrorInvalidValue;
   int most = 0;
