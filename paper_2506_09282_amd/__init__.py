@@ -12,6 +12,7 @@ S = H C^T (Eq. 8), labels = argmax_k S (Eq. 9). Single-pass training
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -154,6 +155,12 @@ def _raise(st: int, where: str):
 _ws_cache: dict = {}
 
 
+@functools.lru_cache(maxsize=1024)
+def _need(query: str, device: int, *sizes) -> int:
+    """A workspace size query's answer (a function of the sizes and the device)."""
+    return int(getattr(lib(), query)(*sizes))
+
+
 def _workspace(device, nbytes: int, key):
     torch = _torch()
     if nbytes == 0:
@@ -245,7 +252,7 @@ def infer(X, B, C, act: str = "hardsign", return_scores: bool = False, out=None,
         labels = torch.empty(N, dtype=torch.int32, device=X.device)
         scores = (torch.empty((N, K), dtype=torch.float32, device=X.device)
                   if return_scores else None)
-    need = int(L.hd_infer_workspace_bytes(N, F, D, K, dt))
+    need = _need("hd_infer_workspace_bytes", X.device.index, N, F, D, K, dt)
     ws = workspace if workspace is not None else _workspace(X.device, need, ("infer", N, F, D, K, dt))
     st = L.hd_infer(X.data_ptr(), B.data_ptr(), C.data_ptr(), labels.data_ptr(),
                     scores.data_ptr() if scores is not None else None, N, F, D, K, dt,
@@ -305,7 +312,7 @@ def infer_packed(X, model: PackedModel, act: str = "hardsign", return_scores: bo
         labels = torch.empty(N, dtype=torch.int32, device=X.device)
         scores = (torch.empty((N, K), dtype=torch.float32, device=X.device)
                   if return_scores else None)
-    need = int(L.hd_infer_packed_workspace_bytes(N, F, D, K, dt))
+    need = _need("hd_infer_packed_workspace_bytes", X.device.index, N, F, D, K, dt)
     ws = workspace if workspace is not None else _workspace(X.device, need,
                                                             ("packed", N, F, D, K, dt))
     st = L.hd_infer_packed(X.data_ptr(), model.image.data_ptr(), labels.data_ptr(),
@@ -372,7 +379,7 @@ def infer_stream(X, model: PackedModel, act: str = "hardsign", return_scores: bo
         labels = torch.empty((nbatch, N), dtype=torch.int32, device=X.device)
         scores = (torch.empty((nbatch, N, K), dtype=torch.float32, device=X.device)
                   if return_scores else None)
-    need = int(L.hd_infer_stream_workspace_bytes(nbatch, N, F, D, K, dt))
+    need = _need("hd_infer_stream_workspace_bytes", X.device.index, nbatch, N, F, D, K, dt)
     if need == 0 and nbatch > 0:
         raise HDError(HD_ERR_UNSUPPORTED, "hd_infer_stream")
     ws = workspace if workspace is not None else _workspace(X.device, need,
