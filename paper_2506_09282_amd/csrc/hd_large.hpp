@@ -423,6 +423,7 @@ __device__ void finish_tile(f32x16 (&sacc)[NTILES][KB], unsigned char* lds,
 // where the registers are full (a spilled register's reload would wait for
 // every buffer-to-LDS load issued before it).
 constexpr int ring_depth(int nfs, int kb) {
+  if (nfs == 49) return 7;  // (nine steps of which are not in registers)
   const int regs = 8 * nfs + 64 + 32 * kb;
   for (int d : {8, 7, 6, 5, 4})
     if (nfs % d == 0 && (d == 4 || regs + 4 * d < 440)) return d;

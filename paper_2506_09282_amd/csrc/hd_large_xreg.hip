@@ -1,5 +1,5 @@
 // Large-batch fused inference with X held in registers (bf16 and int8 rows of
-// up to 40 f-steps): Alg. 4's split of the batch, Stage I and II fused.
+// up to 49 f-steps): Alg. 4's split of the batch, Stage I and II fused.
 //
 // Bound by the matrix cores: dense bf16 work lowers the clock to about
 // 1.8 GHz, so what counts is matrix instructions per cycle and little data
@@ -13,6 +13,8 @@
 // LDS and load B per wave (hd_large.hip): N = 65536, F = 617, D = 10240,
 // K = 26, bf16 762 -> 649 us (1.33 PFLOP/s; the matrix units were waiting on
 // the per-wave B ring), int8 440 -> 358 us; N = 4096 89 -> 70 us, 64 -> 44 us.
+// Rows of 41 to 49 f-steps, a part of X in LDS: F = 784, K = 10, bf16, N = 300
+// 55 -> 34 us, N = 4096 84 -> 74 us, N = 20000 506 -> 298 us.
 #include "hd_large.hpp"
 
 namespace hd {
@@ -39,19 +41,37 @@ constexpr int ring_slots(int nfs, int kb) {
   return r > 8 ? 8 : r;
 }
 
+// Rows of 41 to 49 f-steps leave no registers for every step's X: every fifth
+// step's X (nine of them) then lies in LDS, read two steps ahead, and what LDS
+// is left holds three slots of half a unit each.
+constexpr int kLdsSteps = 9;
+constexpr bool x_in_lds(int nfs, int s) { return nfs > 40 && s % 5 == 4 && s / 5 < kLdsSteps; }
+constexpr int half_frags(int nfs, int kb) { return ((nfs + 2 * kb + 1) / 2 + 3) / 4 * 4; }
+constexpr size_t xreg_lds(int nfs, int kb) {
+  return nfs > 40 ? (size_t)(3 * half_frags(nfs, kb) + kLdsSteps * kNX * kWaves) * 1024
+                  : (size_t)ring_slots(nfs, kb) * unit_frags(nfs, kb) * 1024;
+}
+
 template <class Tr, int NFS, int KB>
 __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
     const typename Tr::elem* __restrict__ X, const uint4* __restrict__ Bp,
     const uint4* __restrict__ Cp, int32_t* __restrict__ labels, float* __restrict__ scores, int N,
     int F, int K, int ndb, int DS, void* __restrict__ workspace) {
   constexpr int DP = ring_depth(NFS, KB);
-  constexpr int UF = unit_frags(NFS, KB);  // fragments per LDS slot
-  constexpr int P = UF / kWaves;           // loads per wave and unit
-  constexpr int R = ring_slots(NFS, KB);
-  constexpr int MID = NFS / 2;
+  constexpr bool HALF = NFS > 40;  // slots of half a unit, nine steps' X in LDS
+  constexpr int UF = HALF ? half_frags(NFS, KB) : unit_frags(NFS, KB);  // fragments per LDS slot
+  constexpr int P = UF / kWaves;  // loads per wave and slot
+  constexpr int R = HALF ? 3 : ring_slots(NFS, KB);
+  constexpr int MID = HALF ? UF / 2 : NFS / 2;
+  constexpr int MID2 = HALF ? UF + (NFS - UF) / 2 : NFS;
   // loads of later units that may be outstanding when the next one must be complete
   constexpr int kOut = P * (R - 3);
   static_assert(NFS % DP == 0 && P <= NFS - MID && R >= 3 && kOut <= 63, "schedule");
+  // halves: the second is complete before its first fragment is read, the
+  // first is read when the second barrier frees its slot, and the next unit's
+  // first is complete before its first fragment is read
+  static_assert(!HALF || (MID <= UF - DP && MID2 >= UF && MID2 <= NFS - DP &&
+                          MID2 + (P + 1) / 2 <= NFS), "schedule");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -66,12 +86,13 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
   const rsrc_t brs = make_rsrc(Bp, b_bytes);
   const rsrc_t crs = make_rsrc(Cp, (uint32_t)ndb * 2 * KB * 1024u);
   const uint32_t lbase = lds_addr(lds);
-  // load p of this wave for unit u into slot: fragment 4p + wave of the unit
-  auto issue = [&](int u, int slot, int p) {
-    const int j = 4 * p + wave;
+  // load p of this wave for unit u into slot: fragment 4p + wave of the unit (of
+  // its half hf)
+  auto issue = [&](int u, int slot, int p, int hf) __attribute__((always_inline)) {
+    const int i = 4 * p + wave, j = i + hf * UF;
     const int db = min(db0 + u, db1 - 1);
-    const uint32_t dst = lbase + (uint32_t)(slot * UF + j) * 1024u;
-    if (4 * p + 3 < NFS || j < NFS) {
+    const uint32_t dst = lbase + (uint32_t)(slot * UF + i) * 1024u;
+    if (hf * UF + 4 * p + 3 < NFS || j < NFS) {
       const uint32_t off = j < nfs ? (uint32_t)(db * nfs + j) * 1024u : b_bytes;
       dma_1k(brs, off + (uint32_t)lane * 16u, dst);
     } else {
@@ -82,7 +103,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
 #pragma unroll
   for (int i = 0; i < R - 1; ++i)
 #pragma unroll
-    for (int p = 0; p < P; ++p) issue(i, i, p);
+    for (int p = 0; p < P; ++p) issue(HALF ? 0 : i, i, p, HALF ? i : 0);
 
   // this wave's rows of X as Stage I operands
   uint4 xf[NFS][kNX];
@@ -156,6 +177,14 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
       for (int r = 0; r < 16; ++r) sacc[t][kb][r] = 0.0f;
 
   const uint4* frag = reinterpret_cast<const uint4*>(lds) + lane;
+  // X of the steps that lie in LDS (each wave its own)
+  uint4* xlds = reinterpret_cast<uint4*>(lds) + (3 * UF + wave * kLdsSteps * kNX) * 64 + lane;
+#pragma unroll
+  for (int s = 0; s < NFS; ++s)
+    if (x_in_lds(NFS, s)) {
+#pragma unroll
+      for (int t = 0; t < kNX; ++t) xlds[(s / 5 * kNX + t) * 64] = xf[s][t];
+    }
   uint4 ring[DP];
 
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
@@ -170,30 +199,51 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
   auto unit = [&](f32x16 (&v)[kNX], const f32x16 (&pv)[kNX], int u, int sl, int sln, int slp,
                   auto first) __attribute__((always_inline)) {
     constexpr bool kFirst = decltype(first)::value;
+    // whole units: slots sl, sln (next), slp (previous); halves: sl and sln hold
+    // this unit, slp the previous one's second half, then the next one's first
     const uint4* fr = frag + sl * (UF * 64);
     const uint4* fn = frag + sln * (UF * 64);
     const uint4* fp = frag + slp * (UF * 64);
     uint4 cf[2][KB];
+    uint4 xl[kNX];
 #pragma unroll
     for (int s = 0; s < NFS; ++s) {
-      if (s == MID)
+      if (s == MID || s == MID2)
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kOut) : "memory");
-      if (s >= MID && s - MID < P) issue(u + R - 1, slp, s - MID);
+      if constexpr (HALF) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          if (s == MID + p / 2) issue(u + 1, slp, p, 0);
+          if (s == MID2 + p / 2) issue(u + 1, sl, p, 1);
+        }
+      } else {
+        if (s >= MID && s - MID < P) issue(u + R - 1, slp, s - MID, 0);
+      }
       const uint4 a = ring[s % DP];
 #pragma unroll
       for (int t = 0; t < kNX; ++t) {
+        const uint4 x = x_in_lds(NFS, s) ? xl[t] : xf[s][t];
         if (s == 0)
-          Tr::stage1_init(v[t], a, xf[s][t]);
+          Tr::stage1_init(v[t], a, x);
         else
-          Tr::stage1(v[t], a, xf[s][t]);
+          Tr::stage1(v[t], a, x);
       }
-      ring[s % DP] = s + DP < NFS ? fr[(s + DP) * 64] : fn[(s + DP - NFS) * 64];
+      if (x_in_lds(NFS, s + 2)) {
+#pragma unroll
+        for (int t = 0; t < kNX; ++t) xl[t] = xlds[((s + 2) / 5 * kNX + t) * 64];
+      }
+      if constexpr (HALF)
+        ring[s % DP] = s + DP < UF    ? fr[(s + DP) * 64]
+                       : s + DP < NFS ? fn[(s + DP - UF) * 64]
+                                      : fp[(s + DP - NFS) * 64];
+      else
+        ring[s % DP] = s + DP < NFS ? fr[(s + DP) * 64] : fn[(s + DP - NFS) * 64];
       if constexpr (!kFirst) {
         if (s < 2) {
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) cf[s][kb] = fp[(NFS + s * KB + kb) * 64];
+          for (int kb = 0; kb < KB; ++kb) cf[s][kb] = fp[(NFS - (HALF ? UF : 0) + s * KB + kb) * 64];
         }
-        constexpr int kStep = MID >= 10 ? (MID - 6) / 4 : 1;  // steps between the four pieces
+        constexpr int kStep = NFS >= 20 ? (NFS / 2 - 6) / 4 : 1;  // steps between the four pieces
         constexpr int kS0 = NFS >= 12 ? 4 : 2;
         if (s >= kS0 && s < kS0 + 4 * kStep && (s - kS0) % kStep == 0) {
           const int p = (s - kS0) / kStep, t = p >> 1, h = p & 1;
@@ -220,7 +270,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
     for (int h = 0; h < 2; ++h) {
       uint4 cf[KB];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) cf[kb] = fp[(NFS + h * KB + kb) * 64];
+      for (int kb = 0; kb < KB; ++kb) cf[kb] = fp[(NFS - (HALF ? UF : 0) + h * KB + kb) * 64];
 #pragma unroll
       for (int t = 0; t < kNX; ++t) {
         uint4 hb;
@@ -239,18 +289,21 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
   int sl = 0;
   auto nxt = [](int s) { return s == R - 1 ? 0 : s + 1; };
   auto prv = [](int s) { return s == 0 ? R - 1 : s - 1; };
+  // A unit's first slot, from the one before: the next slot, or (halves) the one
+  // after its second half's
+  auto adv = [&](int s) { return HALF ? prv(s) : nxt(s); };
   unit(va, va, 0, 0, 1, R - 1, std::true_type{});
   int u = 1;
-  sl = 1;
+  sl = adv(0);
   for (; u + 1 < U; u += 2) {
     unit(vb, va, u, sl, nxt(sl), prv(sl), std::false_type{});
-    sl = nxt(sl);
+    sl = adv(sl);
     unit(va, vb, u + 1, sl, nxt(sl), prv(sl), std::false_type{});
-    sl = nxt(sl);
+    sl = adv(sl);
   }
   if (u < U) {
     unit(vb, va, u, sl, nxt(sl), prv(sl), std::false_type{});
-    tail(vb, sl);
+    tail(vb, HALF ? nxt(sl) : sl);
   } else {
     tail(va, prv(sl));
   }
@@ -301,7 +354,7 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
 
 template <class Tr, int NFS, int KB>
 hipError_t launch_xreg_t(const XregArgs& a, int64_t N, int ds) {
-  constexpr size_t lds = (size_t)ring_slots(NFS, KB) * unit_frags(NFS, KB) * 1024;
+  constexpr size_t lds = xreg_lds(NFS, KB);
   static_assert(lds <= 160 * 1024, "LDS");
   auto* k = &large_fused_kernel_xreg<Tr, NFS, KB>;
   static PerDeviceOnce once;
@@ -316,9 +369,12 @@ hipError_t launch_xreg_t(const XregArgs& a, int64_t N, int ds) {
   return hipGetLastError();
 }
 
-// Instances: unit steps in fours up to max_steps.
+// Instances: unit steps in fours up to max_steps, and 49 for one class block.
+constexpr int most_steps(int kb) { return kb == 1 ? 49 : max_steps(kb); }
+
 template <class Tr, int KB, int NFS = 8>
 hipError_t launch_xreg_steps(int steps, const XregArgs& a, int64_t N, int ds) {
+  if (KB == 1 && steps > 40 && steps <= 49) return launch_xreg_t<Tr, 49, 1>(a, N, ds);
   if constexpr (NFS <= max_steps(KB)) {
     if (steps <= NFS) return launch_xreg_t<Tr, NFS, KB>(a, N, ds);
     return launch_xreg_steps<Tr, KB, NFS + 4>(steps, a, N, ds);
@@ -365,7 +421,7 @@ XregPlan xreg_plan(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act, 
   if (dt == 0 || act != 0 || !x4 || cdiv(K, 32) > 4) return p;
   p.kb = kb_of(K);
   const int64_t steps = dt == 1 ? cdiv(F, TrBF16::kFStep) : cdiv(F, TrI8::kFStep);
-  if (steps > max_steps(p.kb)) return p;
+  if (steps > most_steps(p.kb)) return p;
   const int64_t ndb = cdiv(D, 64) * 2;
   if (ndb * steps * 1024 >= ((int64_t)1 << 31) || ndb * 2 * p.kb * 1024 >= ((int64_t)1 << 31))
     return p;

@@ -53,7 +53,11 @@ CASES = [("bf16", 65, 1, 100, 33), ("bf16", 257, 127, 1000, 32), ("bf16", 256, 1
          ("bf16", 300, 512, 777, 64), ("bf16", 300, 319, 500, 65), ("bf16", 300, 320, 500, 128),
          ("i8", 257, 31, 1000, 32), ("i8", 255, 1279, 500, 5), ("i8", 513, 1280, 64, 10),
          ("i8", 300, 1023, 333, 64), ("i8", 300, 639, 333, 100), ("i8", 300, 33, 100, 17),
-         ("i8", 300, 618, 512, 3)]
+         ("i8", 300, 618, 512, 3),
+         # rows of 41 to 49 f-steps: a part of X in LDS, slots of half a unit
+         ("bf16", 257, 641, 96, 32), ("bf16", 300, 784, 1000, 10), ("bf16", 513, 783, 500, 5),
+         ("bf16", 255, 705, 333, 7), ("i8", 300, 1281, 96, 32), ("i8", 300, 1568, 333, 10),
+         ("i8", 257, 1567, 64, 7)]
 
 
 @pytest.mark.parametrize("dtype,N,F,D,K", CASES)
