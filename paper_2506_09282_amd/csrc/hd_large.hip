@@ -25,8 +25,13 @@
 // (two 32-row MFMA tiles) round-robin within the workgroup's D slice and keeps
 // its own partial S; the waves' partials are summed through LDS at the end.
 // When there are too few sample tiles to fill the GPU, D is also split into
-// DS slices whose partial scores are combined by the last-arriving workgroup
-// of each sample tile (ticket counter, self-cleaning).
+// DS slices whose partial scores a second launch combines in slice order
+// (reduce_slices_kernel).
+//
+// What still runs here: the identity mode, bf16 and int8 rows that the kernel
+// with X in registers does not take (more than 49 f-steps, X not 4-byte
+// aligned), and fp32 models of 2 GiB and more. The packing and the entry points
+// of the path are here too.
 #include <type_traits>
 
 #include "hd_large.hpp"
@@ -164,22 +169,26 @@ __global__ void pack_c_f32(const float* __restrict__ C, uint4* __restrict__ Cp, 
 // Second launch of a call with D split into ds slices: sums the slices'
 // partial scores in slice order (results do not depend on timing), writes the
 // scores, takes the row argmax (lowest index on ties) and clears the
-// workspace again. One thread per (sample, class), 256 / K whole rows per
-// workgroup, 16 slices' loads in flight. A last-arriver reduction inside the
+// workspace again. 256 / K whole rows per workgroup; the slices go to groups of
+// 256 threads, 16 to each, so that all loads of a workgroup are in flight at
+// once (one group took the 64 slices of a small batch in four batches of
+// loads, one latency after the other: 9 us). A last-arriver reduction inside the
 // main kernel has one workgroup per sample tile read every slice with
 // returning atomics: at N = 4096, F = 617, K = 26 (bf16, 16 slices) that call
 // took 135 us.
-__global__ __launch_bounds__(256) void reduce_slices_kernel(float* __restrict__ part,
+__global__ __launch_bounds__(1024) void reduce_slices_kernel(float* __restrict__ part,
                                                             int32_t* __restrict__ labels,
                                                             float* __restrict__ scores, int N,
                                                             int K, int ds) {
-  __shared__ float row[256];
-  const int rpw = 256 / K, tid = threadIdx.x;
+  __shared__ float group_sum[3][256], row[256];
+  const int rpw = 256 / K, tid = threadIdx.x & 255;
+  const int group = threadIdx.x >> 8, groups = blockDim.x >> 8;
   const int64_t i0 = (int64_t)blockIdx.x * rpw * K, total = (int64_t)N * K;
   const int64_t i = i0 + tid;
-  if (tid < rpw * K && i < total) {
-    float s = 0.0f;
-    for (int sl0 = 0; sl0 < ds; sl0 += 16) {
+  const bool mine = tid < rpw * K && i < total;
+  float s = 0.0f;
+  if (mine) {
+    for (int sl0 = 16 * group; sl0 < ds; sl0 += 16 * groups) {
       float t[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) t[j] = sl0 + j < ds ? part[(sl0 + j) * total + i] : 0.0f;
@@ -190,12 +199,17 @@ __global__ __launch_bounds__(256) void reduce_slices_kernel(float* __restrict__ 
           part[(sl0 + j) * total + i] = 0.0f;
         }
     }
+    if (group > 0) group_sum[group - 1][tid] = s;
+  }
+  __syncthreads();
+  if (mine && group == 0) {
+    for (int g = 0; g < groups - 1; ++g) s += group_sum[g][tid];
     row[tid] = s;
     if (scores) scores[i] = s;
   }
   __syncthreads();
   const int64_t n = (int64_t)blockIdx.x * rpw + tid;
-  if (tid < rpw && n < N) {
+  if (group == 0 && tid < rpw && n < N) {
     float best = row[tid * K];
     int best_k = 0;
     for (int k = 1; k < K; ++k) {
@@ -1567,7 +1581,8 @@ hipError_t launch_bundle_dma(const BundleCfg& c, const void* X, const void* pack
 namespace lg {
 hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
                                 int ds, hipStream_t stream) {
-  hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)cdiv(N, 256 / K)), dim3(256), 0, stream,
+  hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)cdiv(N, 256 / K)),
+                     dim3(256u * (ds > 48 ? 4 : ds > 32 ? 3 : ds > 16 ? 2 : 1)), 0, stream,
                      (float*)ws, labels, scores, (int)N, (int)K, ds);
   return hipGetLastError();
 }
