@@ -14,7 +14,7 @@
 // K = 26, bf16 762 -> 649 us (1.33 PFLOP/s; the matrix units were waiting on
 // the per-wave B ring), int8 440 -> 358 us; N = 4096 89 -> 70 us, 64 -> 44 us.
 // Rows of 41 to 49 f-steps, a part of X in LDS: F = 784, K = 10, bf16, N = 300
-// 55 -> 34 us, N = 4096 84 -> 74 us, N = 20000 506 -> 298 us.
+// 55 -> 29 us, N = 4096 84 -> 74 us, N = 20000 506 -> 298 us.
 #include "hd_large.hpp"
 
 namespace hd {
@@ -420,6 +420,11 @@ XregPlan xreg_plan(int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act, 
   XregPlan p{};
   if (dt == 0 || act != 0 || !x4 || cdiv(K, 32) > 4) return p;
   p.kb = kb_of(K);
+  // A few samples of one class block: four waves of which one has samples take
+  // longer to start than the 32-sample tile in LDS (int8 N = 5, F = 1377 34.8
+  // against 31.5 us, bf16 N = 9, F = 690 25.2 against 24.1, as given N = 11,
+  // F = 78 26.8 against 24.4); N = 30, F = 1377 33.5 against 41.5.
+  if (N <= 16 && p.kb == 1) return p;
   const int64_t steps = dt == 1 ? cdiv(F, TrBF16::kFStep) : cdiv(F, TrI8::kFStep);
   if (steps > most_steps(p.kb)) return p;
   const int64_t ndb = cdiv(D, 64) * 2;
