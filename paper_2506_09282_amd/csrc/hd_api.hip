@@ -38,11 +38,12 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // * int8 runs on the fragment kernel only with a packed model (8-10 us for
 //   N <= 64), else on the matrix-core path;
 // * 64 < N <= 256 in fp32 and on a packed bf16 or int8 model: the
-//   matrix-core path has only a few sample tiles (fp32: 138 us for
-//   N = 65..256; bf16: 39-47 us; int8: 33-39 us), while the small path takes
-//   18 us (fp32) or about 10 us (bf16, int8) per 64 samples, so it runs in
-//   64-sample chunks, one after another on the stream, when its 64-sample
-//   plan runs on the matrix cores (not the VALU fallback).
+//   matrix-core path has only a few sample tiles (bf16 N = 300, F = 617: 24 us in its
+//   kernel and about 4 us for the sum of the slices), while the small path takes
+//   18 us (fp32) per 64 samples and about 14 us (bf16) per 128, so it runs in
+//   chunks of 64 (bf16, int8 and room in the workspace: 128), one after
+//   another on the stream, when its 64-sample plan runs on the matrix cores
+//   (not the VALU fallback).
 enum class Route { kSmall, kSmallChunked, kLarge, kNone };
 constexpr int64_t kSmallMaxNBf16 = 8;
 constexpr int64_t kChunkedMaxN = 256;

@@ -1,4 +1,5 @@
-// Small-batch fused inference (N <= 64): the GPU form of the paper's
+// Small-batch fused inference (N <= 64; on bf16 and int8 fragments up to 128, as
+// two passes of 64): the GPU form of the paper's
 // small-batch variant (Sec. III-C, Alg. 3), which splits the hypervector
 // dimension D across workers and sums their partial score matrices.
 //

@@ -57,7 +57,10 @@ CASES = [("bf16", 65, 1, 100, 33), ("bf16", 257, 127, 1000, 32), ("bf16", 256, 1
          # rows of 41 to 49 f-steps: a part of X in LDS, slots of half a unit
          ("bf16", 257, 641, 96, 32), ("bf16", 300, 784, 1000, 10), ("bf16", 513, 783, 500, 5),
          ("bf16", 255, 705, 333, 7), ("i8", 300, 1281, 96, 32), ("i8", 300, 1568, 333, 10),
-         ("i8", 257, 1567, 64, 7)]
+         ("i8", 257, 1567, 64, 7),
+         # D in up to 64 slices, summed by one to four groups; the fewest samples
+         ("bf16", 65, 128, 4096, 33), ("i8", 70, 64, 2500, 17), ("bf16", 17, 690, 4096, 20),
+         ("bf16", 16, 690, 4096, 20)]
 
 
 @pytest.mark.parametrize("dtype,N,F,D,K", CASES)
