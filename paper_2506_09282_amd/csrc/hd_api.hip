@@ -77,7 +77,8 @@ Route route(int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool tiled) {
 }
 
 // Batch size of each small-path launch for a route, at least (any workspace that
-// served 64-sample launches serves the call) or with room for `most`.
+// served 64-sample launches serves the call) or with room for `most`, which
+// takes a packed model and X 16-byte aligned (the fragment kernel).
 int64_t small_n(Route r, int64_t N, int64_t F, int64_t D, int64_t K, int dt, bool most) {
   if (r != Route::kSmallChunked) return N;
   if (!most || !hd::small_two_pass(F, D, K, dt)) return hd::kSmallMaxN;
@@ -251,7 +252,7 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
   if (r == Route::kSmall || r == Route::kSmallChunked) {
     if (dry) return HD_OK;
     if (packed) B = static_cast<const char*>(packed) + image_layout(F, D, K, dt).large;
-    int64_t step = small_n(r, N, F, D, K, dt, packed != nullptr);
+    int64_t step = small_n(r, N, F, D, K, dt, packed && (uintptr_t)X % 16 == 0);
     if (hd::small_workspace_bytes(step, F, D, K, dt, det) > workspace_bytes)
       step = small_n(r, N, F, D, K, dt, false);
     for (int64_t n0 = 0; n0 < N; n0 += step) {
@@ -459,7 +460,8 @@ hd_status hd_infer_packed_noalloc(const void* X, const void* packed, int32_t* la
   const size_t more =
       r == Route::kLarge
           ? hd::large_workspace_used(X, N, F, D, K, dt, act_base(act), kScratchBytes)
-          : hd::small_workspace_bytes(small_n(r, N, F, D, K, dt, true), F, D, K, dt, det_of(act));
+          : hd::small_workspace_bytes(small_n(r, N, F, D, K, dt, (uintptr_t)X % 16 == 0), F, D, K,
+                                      dt, det_of(act));
   const size_t used = more > need && more <= kScratchBytes ? more : need;
   if (used > 0 && hd::launch_zero(ws, used, stream) != hipSuccess) return HD_ERR_HIP;
   return infer_common(X, nullptr, nullptr, packed, labels, scores, N, F, D, K, dt, act, ws,

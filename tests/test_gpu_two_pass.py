@@ -57,3 +57,25 @@ def test_integer_bit_exact(hd, N, F, D, K, dtype, det):
     torch.cuda.synchronize()
     assert np.array_equal(S.cpu().numpy().astype(np.float64), ref["S"])
     assert np.array_equal(y.cpu().numpy(), ref["y"])
+
+
+# X as a slice of a larger tensor: 2-byte aligned only (64-sample calls of the
+# kernel that reads it so); the whole calls, the noalloc one included
+@pytest.mark.parametrize("det", [False, True])
+@pytest.mark.parametrize("shift", [1, 2, 4])
+@pytest.mark.parametrize("N", [65, 100, 128, 250])
+def test_unaligned_bf16_x(hd, N, shift, det):
+    torch = torch_or_skip()
+    F, D, K = 561, 1000, 6
+    announce(f"two pass, X shifted by {shift} N={N} det={det}")
+    X, B, C = hd_inputs.make_integer_inputs(N, F, D, K, seed=N)
+    buf = torch.zeros(N * F + shift, dtype=torch.bfloat16, device="cuda")
+    buf[shift:] = torch.from_numpy(X.reshape(-1)).cuda().to(torch.bfloat16)
+    Xd = buf[shift:].view(N, F)
+    m = hd.pack_model(*(torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (B, C)))
+    ref = oracle.infer(X, B, C)
+    for call in (hd.infer_packed, hd.infer_packed_noalloc):
+        y, S = call(Xd, m, return_scores=True, deterministic=det)
+        torch.cuda.synchronize()
+        assert np.array_equal(S.cpu().numpy().astype(np.float64), ref["S"])
+        assert np.array_equal(y.cpu().numpy(), ref["y"])
