@@ -1,16 +1,18 @@
 // fp32 Stage I on the bf16 matrix instruction, for large batches: inference
 // (Alg. 4) and single-pass training (Sec. II-C), with B packed or as given.
 //
-// Every fp32 value is the exact sum of three bf16 values (its leading, middle
-// and trailing eight significant bits: truncation, so no rounding and no
-// overflow). A product of two values is taken as the six products of parts
-// down to 2^-16 of the leading one, each exact, accumulated in fp32 by
-// v_mfma_f32_32x32x16_bf16; what is left out is below 2^-23 of the product. Six
-// such instructions cost 192 cycles for 16 features against 512 of the fp32
-// instruction.
-// Against 64 bits, signs of X B that differ in 671 million (the fp32
-// instruction in brackets): F = 100 15 (18), 300 10 (33), 561 17 (45), 617 13
-// (36), 784 17 (45), 1500 22 (86), 3072 29 (115).
+// Every fp32 value is the exact sum of three bf16 values: it rounded to bf16,
+// what is left rounded to bf16, and the rest. A product of two values is taken as
+// six of the nine products of parts, each exact, accumulated in fp32 by
+// v_mfma_f32_32x32x16_bf16. The middle part is at most 2^-8 and the trailing one
+// 2^-17 of a value in [1, 2), so the three products left out are together at most
+// 2^-24 of the product, one rounding of the fp32 instruction, of either sign (parts
+// by truncation: up to 2^-21, always towards zero). Six such instructions cost 192
+// cycles for 16 features against 512 of the fp32 instruction.
+// Against 64 bits, signs of X B that differ in 1e9 (normal X; the fp32 instruction
+// 32x32x2 in brackets): F = 4 1.0 (4.2), 16 1.9 (12.7), 32 2.9 (17.0), 100 10 (22),
+// 300 11 (47), 561 19 (75; the streaming kernel's 16x16x4 40), 784 22 (87), 1500
+// 32 (114).
 //
 // Measured (fp32 instruction in brackets; us): inference D = 10240 N = 4096,
 // F = 784, K = 10 packed 317 (601), raw N = 500, F = 617, D = 10000, K = 26 69
@@ -50,19 +52,23 @@ __device__ __forceinline__ bool out_of_range(float m) {
   return m > kHi || (m > 0.0f && m < kLo);  // m: largest magnitude (NaN is not seen: it is exact)
 }
 
+// Two floats rounded to bf16 (v_cvt_pk_bf16_f32), and the floats they stand for.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t round_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float low_of(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float high_of(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
 // Two values into a word of each part (b in the upper half).
 __device__ __forceinline__ void split2(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2,
                                        float& mx) {
-  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
   mx = fmaxf(fmaxf(mx, fabsf(a)), fabsf(b));
-  const float ra = a - __uint_as_float(ua & 0xffff0000u);
-  const float rb = b - __uint_as_float(ub & 0xffff0000u);
-  const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
-  const float sa = ra - __uint_as_float(va & 0xffff0000u);
-  const float sb = rb - __uint_as_float(vb & 0xffff0000u);
-  w0 = __builtin_amdgcn_perm(ub, ua, 0x07060302u);  // the upper halves of (b, a)
-  w1 = __builtin_amdgcn_perm(vb, va, 0x07060302u);
-  w2 = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
+  w0 = round_pair(a, b);
+  const float ra = a - low_of(w0), rb = b - high_of(w0);
+  w1 = round_pair(ra, rb);
+  w2 = round_pair(ra - low_of(w1), rb - high_of(w1));
 }
 
 // Eight values (slot order) into their three parts; mx: running largest magnitude.

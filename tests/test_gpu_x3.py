@@ -1,7 +1,8 @@
 """fp32 Stage I on the bf16 matrix instruction (large batches, training; B packed
-and as given): bit-exact on integer inputs that need all three parts of a
-value, at the edges of its tiles; inputs outside the split's range; and its
-error against float64 next to the fp32 matrix instruction's bound."""
+and as given): bit-exact on integer inputs at the edges of its tiles; products
+of full 24-bit values next to a value that nearly cancels them, which need every
+part and every product of parts; inputs outside the split's range; and the
+fragile-flip rule of every fp32 kernel."""
 from __future__ import annotations
 
 import numpy as np
@@ -22,14 +23,44 @@ def hd():
 
 
 def wide_ints(N, F, D, K, seed):
-    """X up to 2^11, B up to 2^6 / F-dependent, C up to 2^9: values of up to
-    three parts whose sums stay below 2^24."""
+    """X up to 2^11, B up to 2^6 / F-dependent, C up to 2^9: X and C of two parts,
+    sums below 2^24."""
     g = np.random.default_rng(seed)
     bmax = max(1, min(64, (1 << 24) // (F * 2048)))
     X = g.integers(-2047, 2048, (N, F)).astype(np.float32)
     B = g.integers(-bmax, bmax + 1, (F, D)).astype(np.float32)
     C = g.integers(-500, 501, (K, D)).astype(np.float32)
     return X, B, C
+
+
+def near_products(seed, F, D=128):
+    """Rows whose product with column n, x b - c, lies 2^-22 of x b from zero, on
+    either side; x and b with all three parts, half of them with a middle and a
+    trailing part as large as they can be. Returns X, B, C and H[n, n] for n < D
+    (C one-hot: S = H). Each of rounding x b to 24 bits and what the split leaves
+    out is at most 2^-24 of x b, so the sign of x b - c is that of the exact value.
+    Rows past D are scaled copies."""
+    g = np.random.default_rng(seed)
+
+    def mantissas():
+        m = 1.0 + g.integers(0, 1 << 23, D) * 2.0 ** -23
+        # truncation leaves the largest parts below ...11111111b, rounding to
+        # nearest below ...01111111b, in both the lower two parts
+        top = (g.integers(0, 128, D) << 16) | 0xFF00 | g.integers(0xF0, 0x100, D)
+        mid = (g.integers(0, 128, D) << 16) | 0x7F00 | g.integers(0x70, 0x80, D)
+        u = np.where(g.random(D) < 0.5, top, mid)
+        return np.where(g.random(D) < 0.5, m, 1.0 + u * 2.0 ** -23)
+
+    x, b = (mantissas() * g.choice([-1, 1], D) * 2.0 ** g.integers(-6, 7, D) for _ in range(2))
+    p = x * b  # exact: 48 bits
+    c = (p * (1 + g.choice([-1, 1], D) * 2.0 ** -22)).astype(np.float32)
+    n, f = np.arange(D), np.array([g.choice(F, 2, replace=False) for _ in range(D)])
+    X, B = np.zeros((D, F), np.float32), np.zeros((F, D), np.float32)
+    X[n, f[:, 0]], X[n, f[:, 1]] = x, 1.0
+    B[f[:, 0], n], B[f[:, 1], n] = b, -c
+    H = np.where(p >= c.astype(np.float64), 1, -1)
+    X = np.concatenate([X, X * np.float32(2.0), X * np.float32(0.125)])
+    return X, B, np.eye(D, dtype=np.float32), H
 
 
 def run_all(hd, X, B, C, y, K):
@@ -65,6 +96,23 @@ def check(hd, X, B, C, seed):
 def test_integer_bit_exact(hd, N, F, D, K):
     announce(f"x3 N={N} F={F} D={D} K={K}")
     check(hd, *wide_ints(N, F, D, K, N + F), seed=F)
+
+
+@pytest.mark.parametrize("F", [2, 5, 16, 40, 130])
+def test_every_product_of_parts(hd, F):
+    announce(f"x3 near products F={F}")
+    for seed in range(4):
+        X, B, C, H = near_products(seed, F)
+        D = C.shape[0]
+        n = np.arange(D)
+        y = np.concatenate([n, np.full(X.shape[0] - D, -1)]).astype(np.int32)
+        p, r, cp, cr = run_all(hd, X, B, C, y, D)
+        for _, S in (p, r):
+            S = S.cpu().numpy()
+            for i in range(0, X.shape[0], D):
+                assert np.array_equal(S[n + i, n], H)
+        for c in (cp, cr):
+            assert np.array_equal(c.cpu().numpy()[n, n], H)
 
 
 def test_more_tiles_than_compute_units(hd):
