@@ -20,10 +20,13 @@
 // raw 441 (1648, fp32 vector units). About 1.25 PFLOP/s of bf16 products, at the
 // 1.9 GHz that this leaves of the clock.
 //
-// Range. The parts of a value below 2^-110 do not all exist, and inf has none:
-// a pass (128 samples by 256 dimensions) in which a row of X or a column of B
-// has its largest magnitude outside [2^-40, 2^50], unless it is zero, is taken
-// again on the fp32 instruction. The check is part of the split.
+// Range. A value with bits below 2^-133 (some values below 2^-110) is not the sum
+// of its parts: a pass (32 NTILES samples by 256 dimensions) with such a value in a
+// row of X or a column of B is taken again on the fp32 instruction. So is one with a
+// sum that is not finite: inf has no parts, the largest values round to it, and
+// near 2^128 the order of a sum decides. The first check is part of the split (one
+// instruction for two values), the second is on the pass's sums. Both instructions
+// take and give subnormal numbers.
 //
 // Work split. A workgroup holds a tile of 32 NTILES samples; each wave takes one
 // unit of 64 dimensions per pass. B comes from L2 straight into registers (each
@@ -45,12 +48,7 @@ namespace {
 
 // Groups of 16 features per X chunk: one X item (a row's group) per thread.
 constexpr int chunk_groups(int ntiles) { return kThreads / (32 * ntiles); }
-constexpr float kHi = 0x1p50f, kLo = 0x1p-40f;
-constexpr float kCHi = 0x1p50f, kCLo = 0x1p-90f;
-
-__device__ __forceinline__ bool out_of_range(float m) {
-  return m > kHi || (m > 0.0f && m < kLo);  // m: largest magnitude (NaN is not seen: it is exact)
-}
+constexpr float kCHi = 0x1p50f;  // largest |C| in Stage II's three parts
 
 // Two floats rounded to bf16 (v_cvt_pk_bf16_f32), and the floats they stand for.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -61,28 +59,31 @@ __device__ __forceinline__ uint32_t round_pair(float a, float b) {
 __device__ __forceinline__ float low_of(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float high_of(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Two values into a word of each part (b in the upper half).
+// Two values into a word of each part (b in the upper half). rest: the trailing
+// parts' bits so far; a value that is not the sum of its parts leaves one in the
+// lower half.
 __device__ __forceinline__ void split2(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2,
-                                       float& mx) {
-  mx = fmaxf(fmaxf(mx, fabsf(a)), fabsf(b));
+                                       uint32_t& rest) {
   w0 = round_pair(a, b);
   const float ra = a - low_of(w0), rb = b - high_of(w0);
   w1 = round_pair(ra, rb);
-  w2 = round_pair(ra - low_of(w1), rb - high_of(w1));
+  const float sa = ra - low_of(w1), sb = rb - high_of(w1);
+  rest |= __float_as_uint(sa) | __float_as_uint(sb);
+  w2 = round_pair(sa, sb);
 }
 
-// Eight values (slot order) into their three parts; mx: running largest magnitude.
-__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3], float& mx) {
+// Eight values (slot order) into their three parts.
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3], uint32_t& rest) {
   uint32_t w[3][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) split2(x[2 * i], x[2 * i + 1], w[0][i], w[1][i], w[2][i], mx);
+  for (int i = 0; i < 4; ++i) split2(x[2 * i], x[2 * i + 1], w[0][i], w[1][i], w[2][i], rest);
 #pragma unroll
   for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
 }
 
-__device__ __forceinline__ void split8(const float4& a, const float4& b, uint4 (&p)[3], float& mx) {
+__device__ __forceinline__ void split8(const float4& a, const float4& b, uint4 (&p)[3], uint32_t& rest) {
   const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  split8(x, p, mx);
+  split8(x, p, rest);
 }
 
 struct X3Args {
@@ -172,7 +173,7 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   // buffer; lane (n, h) at position (32 h + n) ^ kSw g (the groups of a row are
   // written together: distinct banks). Slot e of half h is feature
   // 8 (e / 4) + 2 (e % 4) + h of the group, as in the packed fp32 fragments of B.
-  auto x_put = [&](int buf, const float4 (&v)[IPT][4], int i, float& mx)
+  auto x_put = [&](int buf, const float4 (&v)[IPT][4], int i, uint32_t& rest)
                    __attribute__((always_inline)) {
     const int row = i * (kThreads / kGC) + tid / kGC;
     unsigned char* dst = lds + buf * kBuf + (xg * NTILES + row / 32) * 3 * 1024;
@@ -181,11 +182,11 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     const float od[8] = {v[i][0].y, v[i][0].w, v[i][1].y, v[i][1].w,
                          v[i][2].y, v[i][2].w, v[i][3].y, v[i][3].w};
     uint4 p[3];
-    split8(ev, p, mx);
+    split8(ev, p, rest);
 #pragma unroll
     for (int q = 0; q < 3; ++q)
       *reinterpret_cast<uint4*>(dst + q * 1024 + ((row % 32) ^ (kSw * xg)) * 16) = p[q];
-    split8(od, p, mx);
+    split8(od, p, rest);
 #pragma unroll
     for (int q = 0; q < 3; ++q)
       *reinterpret_cast<uint4*>(dst + q * 1024 + ((32 + row % 32) ^ (kSw * xg)) * 16) = p[q];
@@ -245,8 +246,8 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   // last phase, for which X is in registers by then, every wave has read what
   // it needs of this chunk and the next one is complete.
   auto group = [&](uint4 (&bp)[2][3], uint4 (&x)[2][3], float4 (&raw)[2][2], int u, int gload,
-                   int buf, int gl, float (&mxb)[2], auto last, float4 (&xv)[IPT][4], int nb,
-                   float (&mxx)[IPT]) __attribute__((always_inline)) {
+                   int buf, int gl, uint32_t (&restb)[2], auto last, float4 (&xv)[IPT][4], int nb,
+                   uint32_t (&restx)[IPT]) __attribute__((always_inline)) {
     constexpr bool kLast = decltype(last)::value;
     constexpr int kPh = NTILES / 2;
     // The matrix instructions go in slices of three with a piece of the other
@@ -261,14 +262,14 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     auto b_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8
       const int b = i >> 2, k = i & 3;
       const float4 v = raw[b][k >> 1];
-      split2(k & 1 ? v.z : v.x, k & 1 ? v.w : v.y, bw[b][0][k], bw[b][1][k], bw[b][2][k], mxb[b]);
+      split2(k & 1 ? v.z : v.x, k & 1 ? v.w : v.y, bw[b][0][k], bw[b][1][k], bw[b][2][k], restb[b]);
       // (computed here, not where it is next used)
       asm volatile("" : "+v"(bw[b][0][k]), "+v"(bw[b][1][k]), "+v"(bw[b][2][k]));
     };
     auto x_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8 IPT
       const int it = i >> 3, odd = (i >> 2) & 1, k = i & 3;
       const float4 v = xv[it][k];
-      split2(odd ? v.y : v.x, odd ? v.w : v.z, xw[0][k], xw[1][k], xw[2][k], mxx[it]);
+      split2(odd ? v.y : v.x, odd ? v.w : v.z, xw[0][k], xw[1][k], xw[2][k], restx[it]);
       asm volatile("" : "+v"(xw[0][k]), "+v"(xw[1][k]), "+v"(xw[2][k]));
       if (k == 3) {
         const int row = it * (kThreads / kGC) + tid / kGC;
@@ -376,10 +377,10 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     }
     x_load(tn, 0, v);
     x_mask(0, v);
-    float mx = 0.0f;
+    uint32_t rest = 0;  // (known already)
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) x_put(0, v, i, mx);
+    for (int i = 0; i < IPT; ++i) x_put(0, v, i, rest);
     __syncthreads();
   };
 
@@ -442,7 +443,8 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     for (int i = 0; i < NTILES; ++i) put_park(i);
   }
   // Stage II of a finished unit: C in three parts against HardSign(V), or on
-  // the fp32 instruction where C's magnitudes ask for it. c0: class block 0.
+  // the fp32 instruction where a value of C is larger than 2^50 or has no three
+  // parts (which are exact against +-1 at any size). c0: class block 0.
   auto stage2 = [&](int u, const float4 (&c0)[2][4]) __attribute__((always_inline)) {
     if constexpr (!TRAIN) {
 #pragma unroll
@@ -457,14 +459,19 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
             for (int q = 0; q < 4; ++q) cv[b][q] = c0[b][q];
         }
         uint4 cp[2][2][3];  // [b][h][part]
-        float mx[2] = {0.0f, 0.0f};
+        uint32_t rest = 0;
+        float mx = 0.0f;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) split8(cv[b][2 * h], cv[b][2 * h + 1], cp[b][h], mx[b]);
-        const bool bad = mx[0] > kCHi || (mx[0] > 0.0f && mx[0] < kCLo) || mx[1] > kCHi ||
-                         (mx[1] > 0.0f && mx[1] < kCLo);
-        const bool native_c = __builtin_amdgcn_ballot_w64(bad) != 0;
+          for (int q = 0; q < 4; ++q)
+            mx = fmaxf(fmaxf(fmaxf(mx, fabsf(cv[b][q].x)), fabsf(cv[b][q].y)),
+                       fmaxf(fabsf(cv[b][q].z), fabsf(cv[b][q].w)));
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) split8(cv[b][2 * h], cv[b][2 * h + 1], cp[b][h], rest);
+        const bool native_c = __builtin_amdgcn_ballot_w64(mx > kCHi || (rest & 0xffffu)) != 0;
 #pragma unroll
         for (int i = 0; i < NTILES; ++i) {
           unpark(i);
@@ -556,9 +563,8 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   float4 xv[IPT][4];
   float4 raw[2][2], r0[2][2];
   uint4 bp[2][3], xc[2][3];
-  float mxb[2], mxx[IPT], mxn[IPT];  // largest magnitudes: columns, rows, the next tile's rows
-#pragma unroll
-  for (int i = 0; i < IPT; ++i) mxx[i] = 0.0f;
+  // trailing parts' bits: columns, rows staged so far, this pass's rows
+  uint32_t restb[2], restx[IPT] = {}, restn[IPT];
   int buf = 0;
   const int npass = TRAIN ? t_end - t_begin : (u_end - u_begin + kWaves - 1) / kWaves;
   // this wave's unit in pass ps (a valid unit when it has none: computed, discarded)
@@ -574,7 +580,7 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   x_load(t_begin, 0, xv);
   x_mask(0, xv);
 #pragma unroll
-  for (int i = 0; i < IPT; ++i) x_put(0, xv, i, mxx[i]);
+  for (int i = 0; i < IPT; ++i) x_put(0, xv, i, restx[i]);
   __syncthreads();
   x_get(0, 0, 0, xc[0]);
   x_get(0, 0, 1, xc[1]);
@@ -585,11 +591,9 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     const int tn = TRAIN ? min(t + 1, t_end - 1) : t;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      mxb[b] = 0.0f;
-      split8(r0[b][0], r0[b][1], bp[b], mxb[b]);
+      restb[b] = 0;
+      split8(r0[b][0], r0[b][1], bp[b], restb[b]);
     }
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) mxn[i] = 0.0f;
 #pragma unroll
     for (int i = 0; i < NTILES; ++i)
 #pragma unroll
@@ -604,37 +608,34 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
       if (lastc) {
 #pragma unroll
         for (int i = 0; i < IPT; ++i) {
-          mxn[i] = mxx[i];
-          mxx[i] = 0.0f;
+          restn[i] = restx[i];
+          restx[i] = 0;
         }
       }
       for (int gl = 0; gl + 1 < ng; ++gl)
-        group(bp, xc, raw, u, g0 + gl + 2, buf, gl, mxb, std::false_type{}, xv, nb, mxx);
+        group(bp, xc, raw, u, g0 + gl + 2, buf, gl, restb, std::false_type{}, xv, nb, restx);
       x_mask(lastc ? 0 : ch + 1, xv);
-      group(bp, xc, raw, u, g0 + ng + 1, buf, ng - 1, mxb, std::true_type{}, xv, nb, mxx);
+      group(bp, xc, raw, u, g0 + ng + 1, buf, ng - 1, restb, std::true_type{}, xv, nb, restx);
       buf = nb;
     }
+    float most = 0.0f;  // largest |sum|, or NaN
 #pragma unroll
     for (int i = 0; i < NTILES; ++i)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) acc[i][b] += low[i][b];
+      for (int b = 0; b < 2; ++b) {
+        acc[i][b] += low[i][b];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+          most = __builtin_elementwise_maximum(
+              most, __builtin_elementwise_maximum(fabsf(acc[i][b][r]), fabsf(acc[i][b][r + 1])));
+      }
     float4 c0[2][4];
     if constexpr (!TRAIN) c_load(u, 0, c0);
     if (ps + 1 < npass) b_start(unit_of(ps + 1));
-    // magnitudes outside the range of the split: the pass again, on fp32.
-    // mxn: this pass's rows (a row's groups lie with kGC threads), mxx: the
-    // rows of the chunk already staged for the next pass
-    bool bad = false;
+    // outside the range of the split: the pass again, on fp32
+    bool bad = !(most < __builtin_huge_valf()) || ((restb[0] | restb[1]) & 0xffffu);
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-      float m = TRAIN ? mxn[i] : fmaxf(mxn[i], mxx[i]);
-#pragma unroll
-      for (int o = 1; o < kGC; o *= 2) m = fmaxf(m, __shfl_xor(m, o, kWave));
-      bad |= out_of_range(m);
-      if constexpr (!TRAIN) mxx[i] = fmaxf(mxn[i], mxx[i]);
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) bad |= out_of_range(fmaxf(mxb[b], __shfl_xor(mxb[b], 32, kWave)));
+    for (int i = 0; i < IPT; ++i) bad |= (restn[i] & 0xffffu) != 0;
     if (__syncthreads_or(bad)) {
       native(u, t, tn);
       buf = 0;

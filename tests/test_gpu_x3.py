@@ -208,6 +208,24 @@ def test_range(hd, what):
     check(hd, X, B, C, seed=9)
 
 
+@pytest.mark.parametrize("side", ["X", "B"])
+def test_parts_that_do_not_exist(hd, side):
+    """Values with bits below 2^-133, which have no three parts, beside ordinary
+    ones that meet zeros: every row and column has its largest magnitude at 1 or
+    more, and the sums are those of the small values alone (exact: integers below
+    2^24 times 2^-149 and 2^-134)."""
+    announce(f"x3 missing parts of {side}")
+    N, F, D, K = 300, 40, 600, 5
+    g = np.random.default_rng(13)
+    for scale in (2.0 ** -149, 2.0 ** -134):
+        small = g.integers(-1000, 1001, (N, F) if side == "X" else (F, D)) * scale
+        other = g.integers(-1, 2, (F, D) if side == "X" else (N, F)).astype(np.float64)
+        X, B = (small, other) if side == "X" else (other, small)
+        X[:, 0], B[0], X[:, 1], B[1] = 3.0, 0.0, 0.0, 5.0
+        C = g.integers(-500, 501, (K, D)).astype(np.float32)
+        check(hd, X.astype(np.float32), B.astype(np.float32), C, seed=13)
+
+
 @pytest.mark.parametrize("N,F,D,K,dist", [(512, 784, 2048, 10, "uniform01_zero20"),
                                           (512, 617, 1500, 26, "normal"),
                                           (300, 3000, 700, 40, "uniform_pm1")])
