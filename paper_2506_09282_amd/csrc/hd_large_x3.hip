@@ -21,12 +21,12 @@
 // 1.9 GHz that this leaves of the clock.
 //
 // Range. A value with bits below 2^-133 (some values below 2^-110) is not the sum
-// of its parts: a pass (32 NTILES samples by 256 dimensions) with such a value in a
-// row of X or a column of B is taken again on the fp32 instruction. So is one with a
-// sum that is not finite: inf has no parts, the largest values round to it, and
-// near 2^128 the order of a sum decides. The first check is part of the split (one
-// instruction for two values), the second is on the pass's sums. Both instructions
-// take and give subnormal numbers.
+// of its parts, inf has no parts, the largest values round to it, and near 2^128
+// the order of a sum decides. So the bits of trailing parts are gathered in the
+// split (one instruction for two values), and the largest sum where its sign is
+// taken; a workgroup that saw such a value, or a sum that is not finite, does its
+// passes again and takes the sums concerned from the fp32 instruction (CAREFUL,
+// below). Both instructions take and give subnormal numbers.
 //
 // Work split. A workgroup holds a tile of 32 NTILES samples; each wave takes one
 // unit of 64 dimensions per pass. B comes from L2 straight into registers (each
@@ -59,17 +59,26 @@ __device__ __forceinline__ uint32_t round_pair(float a, float b) {
 __device__ __forceinline__ float low_of(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float high_of(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Two values into a word of each part (b in the upper half). rest: the trailing
-// parts' bits so far; a value that is not the sum of its parts leaves one in the
-// lower half.
-__device__ __forceinline__ void split2(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2,
-                                       uint32_t& rest) {
+// Two values into a word of each part (b in the upper half), in two halves. rest:
+// the trailing parts' bits so far; a value that is not the sum of its parts leaves
+// one in the lower half.
+__device__ __forceinline__ void split2_lead(float a, float b, uint32_t& w0, float (&r)[2]) {
   w0 = round_pair(a, b);
-  const float ra = a - low_of(w0), rb = b - high_of(w0);
-  w1 = round_pair(ra, rb);
-  const float sa = ra - low_of(w1), sb = rb - high_of(w1);
+  r[0] = a - low_of(w0);
+  r[1] = b - high_of(w0);
+}
+__device__ __forceinline__ void split2_rest(const float (&r)[2], uint32_t& w1, uint32_t& w2,
+                                            uint32_t& rest) {
+  w1 = round_pair(r[0], r[1]);
+  const float sa = r[0] - low_of(w1), sb = r[1] - high_of(w1);
   rest |= __float_as_uint(sa) | __float_as_uint(sb);
   w2 = round_pair(sa, sb);
+}
+__device__ __forceinline__ void split2(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2,
+                                       uint32_t& rest) {
+  float r[2];
+  split2_lead(a, b, w0, r);
+  split2_rest(r, w1, w2, rest);
 }
 
 // Eight values (slot order) into their three parts.
@@ -86,6 +95,9 @@ __device__ __forceinline__ void split8(const float4& a, const float4& b, uint4 (
   split8(x, p, rest);
 }
 
+// Order of the six products, parts of B and of X: lh, mh, mm, hh, hm, hl.
+constexpr int kPartB[6] = {2, 1, 1, 0, 0, 0}, kPartX[6] = {0, 0, 1, 0, 1, 2};
+
 struct X3Args {
   const float* X;
   const void* B;  // packed fragments, or row-major [F][D]
@@ -98,9 +110,10 @@ struct X3Args {
   void* workspace;
 };
 
-// RAW: B (and C) row-major. TRAIN: class sums, else inference.
-template <int NTILES, int KB, bool RAW, bool TRAIN>
-__device__ __forceinline__ void x3_body(const X3Args& a) {
+// RAW: B (and C) row-major. TRAIN: class sums, else inference. Returns true, with
+// nothing written, where the sums are to be taken with CAREFUL (below).
+template <int NTILES, int KB, bool RAW, bool TRAIN, bool CAREFUL>
+__device__ __forceinline__ bool x3_body(const X3Args& a, int tid) {
   constexpr int NT = 32 * NTILES;
   constexpr int kGC = chunk_groups(NTILES);
   constexpr int IPT = NT * kGC / kThreads;  // X items (one row's 16 features) per thread
@@ -110,7 +123,8 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   constexpr int kBuf = kGC * NTILES * 3 * 1024;  // bytes of one X buffer
   static_assert(NTILES % 2 == 0 && IPT == 1 && (!kPark || KB == 1), "tiles in pairs");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  __shared__ unsigned char s_row[NT];  // rows that hold a value that is not the sum of its parts
+  const int lane = tid & 63, half = lane >> 5, col = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = a.N, F = a.F, D = a.D, K = a.K;
   const int G = (F + 15) / 16, nch = (G + kGC - 1) / kGC;
@@ -203,28 +217,28 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   // ---- B: the 16 features of group g, two blocks of 32 dimensions ------------
   const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.B), 0, RAW ? F * D * 4 : 2 * units * nfs8 * 1024, 0x00020000);
+  auto b_load1 = [&](int u, int g, int b, int q, float4& v) __attribute__((always_inline)) {
+    if constexpr (RAW) {
+      // past F the offset is past the matrix (zero); past column D the next row's
+      // values meet zero rows of C, or are not added
+      const int off = ((16 * g + 8 * q + half) * D + 64 * u + 32 * b + col) * 4;
+      float t[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        t[j] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(brs, off + 8 * j * D, 0, 0));
+      v = make_float4(t[0], t[1], t[2], t[3]);
+    } else {
+      const int fs = 2 * g + q;
+      const int off = fs < nfs8 ? ((2 * u + b) * nfs8 + fs) * 1024 + lane * 16 : 0x7ffffff0;
+      v = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brs, off, 0, 0));
+    }
+  };
   auto b_load = [&](int u, int g, float4 (&v)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        if constexpr (RAW) {
-          // past F the offset is past the matrix (zero); past column D the
-          // next row's values meet zero rows of C, or are not added
-          const int off = ((16 * g + 8 * q + half) * D + 64 * u + 32 * b + col) * 4;
-          float t[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            t[j] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(brs, off + 8 * j * D, 0, 0));
-          v[b][q] = make_float4(t[0], t[1], t[2], t[3]);
-        } else {
-          const int fs = 2 * g + q;
-          const int off = fs < nfs8 ? ((2 * u + b) * nfs8 + fs) * 1024 + lane * 16 : 0x7ffffff0;
-          v[b][q] = __builtin_bit_cast(float4,
-                                       __builtin_amdgcn_raw_buffer_load_b128(brs, off, 0, 0));
-        }
-      }
+      for (int q = 0; q < 2; ++q) b_load1(u, g, b, q, v[b][q]);
   };
 
   // The leading parts' products and the others' are summed apart: the others
@@ -250,77 +264,82 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
                    uint32_t (&restx)[IPT]) __attribute__((always_inline)) {
     constexpr bool kLast = decltype(last)::value;
     constexpr int kPh = NTILES / 2;
-    // The matrix instructions go in slices of three with a piece of the other
-    // work behind each (a slice is 96 cycles, a pair's split about 12
-    // instructions of 4): left to itself the compiler gathers the splits in
-    // blocks that the matrix unit waits for (346 against 323 us at N = 4096,
-    // F = 784, D = 10240, K = 10).
-    constexpr int kSlices = 8 * kPh;        // of the group
-    constexpr int kBar = kSlices - 4;       // the barrier's slice
+    // Behind each matrix instruction (32 cycles, of which it takes 4 to issue) goes
+    // half a pair's split, five or seven instructions of 4 cycles, and a load or two:
+    // left to itself the compiler gathers the splits in blocks that the matrix unit
+    // waits for.
+    constexpr int kSlots = 24 * kPh;
+    constexpr int kBar = kSlots - 12;                   // the barrier's slot
+    constexpr int kXSlots = kPh == 1 ? 12 : 24;         // X's 16 halves: the first slots
+    constexpr int kB0 = kPh == 1 ? 12 : 24, kBSlots = kPh == 1 ? 12 : 16;  // B's halves
     uint32_t bw[2][3][4], xw[3][4];
     uint4 xn[2][3];
-    auto b_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8
-      const int b = i >> 2, k = i & 3;
-      const float4 v = raw[b][k >> 1];
-      split2(k & 1 ? v.z : v.x, k & 1 ? v.w : v.y, bw[b][0][k], bw[b][1][k], bw[b][2][k], restb[b]);
-      // (computed here, not where it is next used)
-      asm volatile("" : "+v"(bw[b][0][k]), "+v"(bw[b][1][k]), "+v"(bw[b][2][k]));
-    };
-    auto x_piece = [&](int i) __attribute__((always_inline)) {  // pair i of 8 IPT
-      const int it = i >> 3, odd = (i >> 2) & 1, k = i & 3;
-      const float4 v = xv[it][k];
-      split2(odd ? v.y : v.x, odd ? v.w : v.z, xw[0][k], xw[1][k], xw[2][k], restx[it]);
-      asm volatile("" : "+v"(xw[0][k]), "+v"(xw[1][k]), "+v"(xw[2][k]));
-      if (k == 3) {
-        const int row = it * (kThreads / kGC) + tid / kGC;
-        unsigned char* dst = lds + nb * kBuf + (xg * NTILES + row / 32) * 3 * 1024 +
-                             ((32 * odd + row % 32) ^ (kSw * xg)) * 16;
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          *reinterpret_cast<uint4*>(dst + q * 1024) =
-              make_uint4(xw[q][0], xw[q][1], xw[q][2], xw[q][3]);
+    float br[2], xr[2];
+    // half h of B's 16: pair h / 2 is (k, k + 1) of block b; a fragment's registers
+    // take the next one once both of its pairs are read
+    auto b_half = [&](int h) __attribute__((always_inline)) {
+      const int b = h >> 3, k = (h >> 1) & 3;
+      if (h % 2 == 0) {
+        const float4 v = raw[b][k >> 1];
+        split2_lead(k & 1 ? v.z : v.x, k & 1 ? v.w : v.y, bw[b][0][k], br);
+        // (computed here, not where it is next used)
+        asm volatile("" : "+v"(bw[b][0][k]), "+v"(br[0]), "+v"(br[1]));
+        if (k & 1) b_load1(u, gload, b, k >> 1, raw[b][k >> 1]);
+      } else {
+        split2_rest(br, bw[b][1][k], bw[b][2][k], restb[b]);
+        asm volatile("" : "+v"(bw[b][1][k]), "+v"(bw[b][2][k]));
       }
     };
-    // parts (B, X): lh, mh, mm, hh, hm, hl. B's trailing and middle parts are
-    // done with by the barrier's slice, where the next group's take over
-    // their registers.
-    constexpr int pb[6] = {2, 1, 1, 0, 0, 0}, px[6] = {0, 0, 1, 0, 1, 2};
+    auto x_half = [&](int h) __attribute__((always_inline)) {  // half h of X's 16
+      const int odd = h >> 3, k = (h >> 1) & 3;
+      if (h % 2 == 0) {
+        const float4 v = xv[0][k];
+        split2_lead(odd ? v.y : v.x, odd ? v.w : v.z, xw[0][k], xr);
+        asm volatile("" : "+v"(xw[0][k]), "+v"(xr[0]), "+v"(xr[1]));
+      } else {
+        split2_rest(xr, xw[1][k], xw[2][k], restx[0]);
+        asm volatile("" : "+v"(xw[1][k]), "+v"(xw[2][k]));
+        if (k == 3) {
+          const int row = tid / kGC;
+          unsigned char* dst = lds + nb * kBuf + (xg * NTILES + row / 32) * 3 * 1024 +
+                               ((32 * odd + row % 32) ^ (kSw * xg)) * 16;
 #pragma unroll
-    for (int sl = 0; sl < kSlices; ++sl) {
-      const int ph = sl >> 3, ss = sl & 7;
-#pragma unroll
-      for (int m = 3 * ss; m < 3 * ss + 3; ++m) {
-        const int c = m >> 2, t = (m >> 1) & 1, b = m & 1;
-        mma(bp[b][pb[c]], x[t][px[c]], c == 3 ? acc[2 * ph + t][b] : low[2 * ph + t][b]);
-      }
-      if (kLast && sl == kBar) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      // X of the next phase, two fragments behind each of three slices
-      const int rd = ph + 1 < kPh || !kLast ? ss : sl - kBar;
-      if (rd >= 0 && rd < 3) {
-        if (ph + 1 < kPh) {
-          x_get1(buf, gl, 2 * ph + 2, rd, xn[0][rd]);
-          x_get1(buf, gl, 2 * ph + 3, rd, xn[1][rd]);
-        } else {
-          x_get1(kLast ? nb : buf, kLast ? 0 : gl + 1, 0, rd, xn[0][rd]);
-          x_get1(kLast ? nb : buf, kLast ? 0 : gl + 1, 1, rd, xn[1][rd]);
+          for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<uint4*>(dst + q * 1024) =
+                make_uint4(xw[q][0], xw[q][1], xw[q][2], xw[q][3]);
         }
       }
+    };
+    // B's trailing and middle parts are done with by the barrier's slot, where the
+    // next group's take over their registers.
+#pragma unroll
+    for (int sl = 0; sl < kSlots; ++sl) {
+      const int ph = sl / 24, m = sl % 24, c = m >> 2, t = (m >> 1) & 1, b = m & 1;
+      mma(bp[b][kPartB[c]], x[t][kPartX[c]], c == 3 ? acc[2 * ph + t][b] : low[2 * ph + t][b]);
+      if (kLast && sl == kBar) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      // X of the next phase, a fragment behind each of six
+      const int rd = ph + 1 < kPh || !kLast ? m : sl - kBar;
+      if (rd >= 0 && rd < 6) {
+        if (ph + 1 < kPh)
+          x_get1(buf, gl, 2 * ph + 2 + (rd & 1), rd >> 1, xn[rd & 1][rd >> 1]);
+        else
+          x_get1(kLast ? nb : buf, kLast ? 0 : gl + 1, rd & 1, rd >> 1, xn[rd & 1][rd >> 1]);
+      }
       if constexpr (kLast) {
-        constexpr int kX = 8 * IPT;
 #pragma unroll
-        for (int i = sl * kX / kBar; i < (sl + 1) * kX / kBar && i < kX; ++i) x_piece(i);
+        for (int h = sl * 16 / kXSlots; h < (sl + 1) * 16 / kXSlots && h < 16; ++h) x_half(h);
       }
-      if (sl >= kBar) {
-        b_piece(2 * (sl - kBar));
-        b_piece(2 * (sl - kBar) + 1);
+      if (sl >= kB0) {
+#pragma unroll
+        for (int h = (sl - kB0) * 16 / kBSlots; h < (sl - kB0 + 1) * 16 / kBSlots && h < 16; ++h)
+          b_half(h);
       }
-      if (sl == kSlices - 1) b_load(u, gload, raw);
       __builtin_amdgcn_sched_barrier(0);
-      if (ss == 7) {
+      if (m == 23) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
-          for (int q = 0; q < 3; ++q) x[t][q] = xn[t][q];
+          for (int q = 0; q < 3; ++q) x[t2][q] = xn[t2][q];
       }
     }
 #pragma unroll
@@ -330,74 +349,11 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
         bp[b][q] = make_uint4(bw[b][q][0], bw[b][q][1], bw[b][q][2], bw[b][q][3]);
   };
 
-  // The pass again on the fp32 matrix instruction: X as fp32 in LDS, nothing
-  // overlapped. Leaves the chunk-0 parts of tile tn in buffer 0.
-  auto native = [&](int u, int t, int tn) {
-    constexpr int kPitch = kGC * 16 + 4;  // floats per row
-    float* xf = reinterpret_cast<float*>(lds);
-#pragma unroll
-    for (int i = 0; i < NTILES; ++i)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][b][r] = 0.0f;
-    float4 v[IPT][4];
-    for (int ch = 0; ch < nch; ++ch) {
-      x_load(t, ch, v);
-      x_mask(ch, v);
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < IPT; ++i) {
-        float* dst = xf + (i * (kThreads / kGC) + tid / kGC) * kPitch + xg * 16;
-        reinterpret_cast<float4*>(dst)[0] = make_float4(v[i][0].x, v[i][0].z, v[i][1].x, v[i][1].z);
-        reinterpret_cast<float4*>(dst)[1] = make_float4(v[i][0].y, v[i][0].w, v[i][1].y, v[i][1].w);
-        reinterpret_cast<float4*>(dst)[2] = make_float4(v[i][2].x, v[i][2].z, v[i][3].x, v[i][3].z);
-        reinterpret_cast<float4*>(dst)[3] = make_float4(v[i][2].y, v[i][2].w, v[i][3].y, v[i][3].w);
-      }
-      __syncthreads();
-      const int ng = min(kGC, G - ch * kGC);
-      for (int gl = 0; gl < ng; ++gl) {
-        float4 bv[2][2];
-        b_load(u, ch * kGC + gl, bv);
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int i = 0; i < NTILES; ++i) {
-            const uint4 x = *reinterpret_cast<const uint4*>(xf + (32 * i + col) * kPitch + gl * 16 +
-                                                            8 * q + 4 * half);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              if constexpr (TRAIN)
-                TrF32::stage1(acc[i][b], x, bitcast<uint4>(bv[b][q]));
-              else
-                TrF32::stage1(acc[i][b], bitcast<uint4>(bv[b][q]), x);
-            }
-          }
-      }
-    }
-    x_load(tn, 0, v);
-    x_mask(0, v);
-    uint32_t rest = 0;  // (known already)
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) x_put(0, v, i, rest);
-    __syncthreads();
-  };
-
   // ---- scores or class sums ---------------------------------------------------
   f32x4* park = reinterpret_cast<f32x4*>(lds + 2 * kBuf) + wave * (NTILES * 4 * 64) + lane;
   f32x16 sacc[TRAIN ? 1 : NTILES][KB];  // S^T of this wave's units
   i32x16 cacc[TRAIN ? 2 : 1][KB];       // class sums of this wave's unit
-#pragma unroll
-  for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-#pragma unroll
-      for (int i = 0; i < (TRAIN ? 1 : NTILES); ++i) sacc[i][kb][r] = 0.0f;
-#pragma unroll
-      for (int i = 0; i < (TRAIN ? 2 : 1); ++i) cacc[i][kb][r] = 0;
-    }
-
+  float most = 0.0f;                    // largest |V| of all passes, or NaN
   // The C values of class block kb against the unit's dimensions.
   auto c_load = [&](int u, int kb, float4 (&cv)[2][4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -438,10 +394,30 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
                                        sacc[i][0][4 * q + 2], sacc[i][0][4 * q + 3]};
     }
   };
-  if constexpr (kPark) {
+  auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NTILES; ++i) put_park(i);
-  }
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+#pragma unroll
+        for (int i = 0; i < (TRAIN ? 1 : NTILES); ++i) sacc[i][kb][r] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < (TRAIN ? 2 : 1); ++i) cacc[i][kb][r] = 0;
+      }
+    if constexpr (kPark) {
+#pragma unroll
+      for (int i = 0; i < NTILES; ++i) put_park(i);
+    }
+  };
+  clear_sums();
+  auto note_most = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2)
+        most = __builtin_elementwise_maximum(
+            most, __builtin_elementwise_maximum(fabsf(acc[i][b][r]), fabsf(acc[i][b][r + 1])));
+  };
   // Stage II of a finished unit: C in three parts against HardSign(V), or on
   // the fp32 instruction where a value of C is larger than 2^50 or has no three
   // parts (which are exact against +-1 at any size). c0: class block 0.
@@ -475,6 +451,7 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
 #pragma unroll
         for (int i = 0; i < NTILES; ++i) {
           unpark(i);
+          if (kb == 0) note_most(i);
           if (!native_c) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
@@ -530,6 +507,7 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
             for (int j = 0; j < 4; ++j)
               if (32 * i + 8 * q + 4 * half + j >= rows) yl[4 * q + j] = -1;
         }
+        note_most(i);
         i32x4 h[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -559,97 +537,213 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
   };
 
   // ---- passes -------------------------------------------------------------------
-  if (t_begin >= t_end || u_begin >= u_end) return;
-  float4 xv[IPT][4];
-  float4 raw[2][2], r0[2][2];
-  uint4 bp[2][3], xc[2][3];
-  // trailing parts' bits: columns, rows staged so far, this pass's rows
-  uint32_t restb[2], restx[IPT] = {}, restn[IPT];
-  int buf = 0;
+  if (t_begin >= t_end || u_begin >= u_end) return false;
   const int npass = TRAIN ? t_end - t_begin : (u_end - u_begin + kWaves - 1) / kWaves;
   // this wave's unit in pass ps (a valid unit when it has none: computed, discarded)
   auto unit_of = [&](int ps) {
     const int u = TRAIN ? u_begin + wave : u_begin + ps * kWaves + wave;
     return u < u_end ? u : u_begin;
   };
-  auto b_start = [&](int u) __attribute__((always_inline)) {
-    b_load(u, 0, r0);
-    b_load(u, 1, raw);
-  };
-  b_start(unit_of(0));
-  x_load(t_begin, 0, xv);
-  x_mask(0, xv);
+  if constexpr (CAREFUL) {
+    // All passes again: the same products in the same order, nothing overlapped, and
+    // then on the fp32 matrix instruction, from which a sum is taken if its row or
+    // its column holds a value that is not the sum of its parts, or if it is not
+    // finite. So a sample's result does not depend on its neighbours. (Of the other
+    // sums the sign is kept meanwhile.)
+    constexpr int kPitch = kGC * 16 + 4;  // floats per row
+    float* xf = reinterpret_cast<float*>(lds);
+    for (int ps = 0; ps < npass; ++ps) {
+      const int t = TRAIN ? t_begin + ps : t_begin;
+      const int u = unit_of(ps);
+      auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < IPT; ++i) x_put(0, xv, i, restx[i]);
-  __syncthreads();
-  x_get(0, 0, 0, xc[0]);
-  x_get(0, 0, 1, xc[1]);
-
-  for (int ps = 0; ps < npass; ++ps) {
-    const int t = TRAIN ? t_begin + ps : t_begin;
-    const int u = unit_of(ps);
-    const int tn = TRAIN ? min(t + 1, t_end - 1) : t;
+        for (int i = 0; i < NTILES; ++i)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      restb[b] = 0;
-      split8(r0[b][0], r0[b][1], bp[b], restb[b]);
-    }
+          for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int i = 0; i < NTILES; ++i)
+            for (int r = 0; r < 16; ++r) acc[i][b][r] = low[i][b][r] = 0.0f;
+      };
+      clear();
+      uint32_t restb[2] = {}, restx[IPT] = {};
+      float4 v[IPT][4], bv[2][2];
+      for (int ch = 0; ch < nch; ++ch) {
+        x_load(t, ch, v);
+        x_mask(ch, v);
+        __syncthreads();
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+        for (int i = 0; i < IPT; ++i) x_put(0, v, i, restx[i]);
+        __syncthreads();
+        const int ng = min(kGC, G - ch * kGC);
+        for (int gl = 0; gl < ng; ++gl) {
+          uint4 bp[2][3], x[3];
+          b_load(u, ch * kGC + gl, bv);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][b][r] = low[i][b][r] = 0.0f;
-    for (int ch = 0; ch < nch; ++ch) {
-      const bool lastc = ch + 1 == nch;
-      const int nb = buf ^ 1, ng = min(kGC, G - ch * kGC), g0 = ch * kGC;
-      // next chunk of X: of this tile, or the first of the next pass's tile
-      x_load(lastc ? tn : t, lastc ? 0 : ch + 1, xv);
-      if (lastc) {
+          for (int b = 0; b < 2; ++b) split8(bv[b][0], bv[b][1], bp[b], restb[b]);
 #pragma unroll
-        for (int i = 0; i < IPT; ++i) {
-          restn[i] = restx[i];
-          restx[i] = 0;
+          for (int i = 0; i < NTILES; ++i) {
+            x_get(0, gl, i, x);
+#pragma unroll
+            for (int c = 0; c < 6; ++c)
+#pragma unroll
+              for (int b = 0; b < 2; ++b)
+                mma(bp[b][kPartB[c]], x[kPartX[c]], c == 3 ? acc[i][b] : low[i][b]);
+          }
         }
       }
-      for (int gl = 0; gl + 1 < ng; ++gl)
-        group(bp, xc, raw, u, g0 + gl + 2, buf, gl, restb, std::false_type{}, xv, nb, restx);
-      x_mask(lastc ? 0 : ch + 1, xv);
-      group(bp, xc, raw, u, g0 + ng + 1, buf, ng - 1, restb, std::true_type{}, xv, nb, restx);
-      buf = nb;
-    }
-    float most = 0.0f;  // largest |sum|, or NaN
+      // Which sums are taken from the fp32 instruction, and the others' signs: bit
+      // 16 b + r of tile i's word for sum r of block b.
+      if (tid < NT) s_row[tid] = 0;
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NTILES; ++i)
+      for (int i = 0; i < IPT; ++i)
+        if (restx[i] & 0xffffu) s_row[i * (kThreads / kGC) + tid / kGC] = 1;
+      __syncthreads();
+      uint32_t pos[NTILES], again[NTILES], cols[2];
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        acc[i][b] += low[i][b];
-#pragma unroll
-        for (int r = 0; r < 16; r += 2)
-          most = __builtin_elementwise_maximum(
-              most, __builtin_elementwise_maximum(fabsf(acc[i][b][r]), fabsf(acc[i][b][r + 1])));
+        const uint64_t m = __builtin_amdgcn_ballot_w64((restb[b] & 0xffffu) != 0);
+        cols[b] = (uint32_t)m | (uint32_t)(m >> 32);
       }
-    float4 c0[2][4];
-    if constexpr (!TRAIN) c_load(u, 0, c0);
-    if (ps + 1 < npass) b_start(unit_of(ps + 1));
-    // outside the range of the split: the pass again, on fp32
-    bool bad = !(most < __builtin_huge_valf()) || ((restb[0] | restb[1]) & 0xffffu);
+      bool any = false;
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) bad |= (restn[i] & 0xffffu) != 0;
-    if (__syncthreads_or(bad)) {
-      native(u, t, tn);
-      buf = 0;
-      x_get(0, 0, 0, xc[0]);
-      x_get(0, 0, 1, xc[1]);
+      for (int i = 0; i < NTILES; ++i) {
+        const uint32_t rows = (uint32_t)__builtin_amdgcn_ballot_w64(s_row[32 * i + col] != 0);
+        pos[i] = again[i] = 0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          // this lane's bit of what lies in lanes, the register's of what lies in rows
+          const uint32_t mine = (TRAIN ? cols[b] : rows) >> col & 1u;
+          const uint32_t regs = (TRAIN ? rows : cols[b]) >> (4 * half);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float a = acc[i][b][r] + low[i][b][r];
+            const bool from = mine | (regs >> (8 * (r >> 2) + (r & 3)) & 1u) |
+                              !(fabsf(a) < __builtin_huge_valf());
+            pos[i] |= a >= 0.0f ? 1u << (16 * b + r) : 0u;
+            again[i] |= from ? 1u << (16 * b + r) : 0u;
+          }
+        }
+        any |= again[i] != 0;
+      }
+      clear();
+      if (__syncthreads_or(any)) {
+        for (int ch = 0; ch < nch; ++ch) {
+          x_load(t, ch, v);
+          x_mask(ch, v);
+          __syncthreads();
+#pragma unroll
+          for (int i = 0; i < IPT; ++i) {
+            float4* dst = reinterpret_cast<float4*>(
+                xf + (i * (kThreads / kGC) + tid / kGC) * kPitch + xg * 16);
+            dst[0] = make_float4(v[i][0].x, v[i][0].z, v[i][1].x, v[i][1].z);
+            dst[1] = make_float4(v[i][0].y, v[i][0].w, v[i][1].y, v[i][1].w);
+            dst[2] = make_float4(v[i][2].x, v[i][2].z, v[i][3].x, v[i][3].z);
+            dst[3] = make_float4(v[i][2].y, v[i][2].w, v[i][3].y, v[i][3].w);
+          }
+          __syncthreads();
+          const int ng = min(kGC, G - ch * kGC);
+          for (int gl = 0; gl < ng; ++gl) {
+            b_load(u, ch * kGC + gl, bv);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+              for (int i = 0; i < NTILES; ++i) {
+                const uint4 x = *reinterpret_cast<const uint4*>(
+                    xf + (32 * i + col) * kPitch + gl * 16 + 8 * q + 4 * half);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                  if constexpr (TRAIN)
+                    TrF32::stage1(acc[i][b], x, bitcast<uint4>(bv[b][q]));
+                  else
+                    TrF32::stage1(acc[i][b], bitcast<uint4>(bv[b][q]), x);
+                }
+              }
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float was = pos[i] >> (16 * b + r) & 1u ? 1.0f : -1.0f;
+            acc[i][b][r] = again[i] >> (16 * b + r) & 1u ? acc[i][b][r] : was;
+          }
+      if constexpr (TRAIN) {
+        class_sums(t);
+      } else if (u_begin + ps * kWaves + wave < u_end) {
+        float4 c0[2][4];
+        c_load(u, 0, c0);
+        stage2(u, c0);
+      }
     }
-    if constexpr (TRAIN)
-      class_sums(t);
-    else if (u_begin + ps * kWaves + wave < u_end)
-      stage2(u, c0);
+  } else {
+    float4 xv[IPT][4];
+    float4 raw[2][2], r0[2][2];
+    uint4 bp[2][3], xc[2][3];
+    uint32_t restb[2] = {}, restx[IPT] = {};  // trailing parts' bits of all passes
+    int buf = 0;
+    auto b_start = [&](int u) __attribute__((always_inline)) {
+      b_load(u, 0, r0);
+      b_load(u, 1, raw);
+    };
+    b_start(unit_of(0));
+    x_load(t_begin, 0, xv);
+    x_mask(0, xv);
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) x_put(0, xv, i, restx[i]);
+    __syncthreads();
+    x_get(0, 0, 0, xc[0]);
+    x_get(0, 0, 1, xc[1]);
+
+    for (int ps = 0; ps < npass; ++ps) {
+      const int t = TRAIN ? t_begin + ps : t_begin;
+      const int u = unit_of(ps);
+      const int tn = TRAIN ? min(t + 1, t_end - 1) : t;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        split8(r0[b][0], r0[b][1], bp[b], restb[b]);
+      }
+#pragma unroll
+      for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][b][r] = low[i][b][r] = 0.0f;
+      for (int ch = 0; ch < nch; ++ch) {
+        const bool lastc = ch + 1 == nch;
+        const int nb = buf ^ 1, ng = min(kGC, G - ch * kGC), g0 = ch * kGC;
+        // next chunk of X: of this tile, or the first of the next pass's tile
+        x_load(lastc ? tn : t, lastc ? 0 : ch + 1, xv);
+        for (int gl = 0; gl + 1 < ng; ++gl)
+          group(bp, xc, raw, u, g0 + gl + 2, buf, gl, restb, std::false_type{}, xv, nb, restx);
+        x_mask(lastc ? 0 : ch + 1, xv);
+        group(bp, xc, raw, u, g0 + ng + 1, buf, ng - 1, restb, std::true_type{}, xv, nb, restx);
+        buf = nb;
+      }
+#pragma unroll
+      for (int i = 0; i < NTILES; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[i][b] += low[i][b];
+      float4 c0[2][4];
+      if constexpr (!TRAIN) c_load(u, 0, c0);
+      if (ps + 1 < npass) b_start(unit_of(ps + 1));
+      if constexpr (TRAIN)
+        class_sums(t);
+      else if (u_begin + ps * kWaves + wave < u_end)
+        stage2(u, c0);
+    }
+
+    // outside the range of the split
+    uint32_t rest = restb[0] | restb[1];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) rest |= restx[i];
+    if (__syncthreads_or((rest & 0xffffu) || !(most < __builtin_huge_valf()))) return true;
   }
 
   if constexpr (TRAIN) {
-    if (u_begin + wave >= u_end) return;
+    if (u_begin + wave >= u_end) return false;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int d = 64 * (u_begin + wave) + 32 * b + col;
@@ -669,16 +763,28 @@ __device__ __forceinline__ void x3_body(const X3Args& a) {
     finish_tile<NTILES, KB>(sacc, lds, a.labels, a.scores, N, K, a.DS, slice, t_begin * NT,
                             a.workspace);
   }
+  return false;
+}
+
+// The careful form starts from a thread index of its own, which the compiler does
+// not know to be the same: it would keep what both compute from it in registers.
+template <int NTILES, int KB, bool RAW, bool TRAIN>
+__device__ __forceinline__ void x3_kernel(const X3Args& a) {
+  if (__builtin_expect(x3_body<NTILES, KB, RAW, TRAIN, false>(a, threadIdx.x), 0)) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    x3_body<NTILES, KB, RAW, TRAIN, true>(a, tid);
+  }
 }
 
 template <int NTILES, int KB, bool RAW>
 __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_x3(X3Args a) {
-  x3_body<NTILES, KB, RAW, false>(a);
+  x3_kernel<NTILES, KB, RAW, false>(a);
 }
 
 template <int NTILES, int KB, bool RAW>
 __global__ __launch_bounds__(kThreads, 1) void bundle_mfma_kernel_x3(X3Args a) {
-  x3_body<NTILES, KB, RAW, true>(a);
+  x3_kernel<NTILES, KB, RAW, true>(a);
 }
 
 constexpr size_t x3_lds(int ntiles, int kb, bool train) {

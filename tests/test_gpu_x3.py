@@ -226,6 +226,42 @@ def test_parts_that_do_not_exist(hd, side):
         check(hd, X.astype(np.float32), B.astype(np.float32), C, seed=13)
 
 
+def test_neighbours_do_not_matter(hd):
+    """Sums within rounding of zero, whose signs the two instructions take
+    differently: a row or a column that needs the fp32 instruction changes no
+    other row's or column's signs."""
+    announce("x3 neighbours")
+    N, F, D, K = 384, 48, 8256, 5
+    g = np.random.default_rng(17)
+    x = g.standard_normal(F).astype(np.float32)
+    x[-1] = 1.0
+    X = (x * 2.0 ** g.integers(-3, 4, (N, 1))).astype(np.float32)
+    B = g.standard_normal((F, D)).astype(np.float32)
+    B[-1] = -(x[:-1].astype(np.float64) @ B[:-1].astype(np.float64))
+    C = g.integers(-500, 501, (K, D)).astype(np.float32)
+    y = g.integers(0, K, N).astype(np.int32)
+    y[7] = -1
+    base = [t if isinstance(t, tuple) else (t,) for t in run_all(hd, X, B, C, y, K)]
+    rows, cols = np.arange(N) != 7, np.arange(D) != 300
+    for what in ("row", "column"):
+        X2, B2, C2 = X.copy(), B.copy(), C.copy()
+        if what == "row":
+            X2[7, 3] = np.inf
+        else:
+            B2[5, 300] = np.inf
+            C2[:, 300] = 0
+            base = [t if isinstance(t, tuple) else (t,) for t in run_all(hd, X, B, C2, y, K)]
+        got = [t if isinstance(t, tuple) else (t,) for t in run_all(hd, X2, B2, C2, y, K)]
+        for k in range(2):  # packed, raw
+            for a, b in zip(base[k], got[k]):
+                a, b = a.cpu().numpy(), b.cpu().numpy()
+                assert np.array_equal(a[rows] if what == "row" else a,
+                                      b[rows] if what == "row" else b), (what, k)
+            a, b = base[2 + k][0].cpu().numpy(), got[2 + k][0].cpu().numpy()
+            assert np.array_equal(a if what == "row" else a[:, cols],
+                                  b if what == "row" else b[:, cols]), (what, k)
+
+
 @pytest.mark.parametrize("N,F,D,K,dist", [(512, 784, 2048, 10, "uniform01_zero20"),
                                           (512, 617, 1500, 26, "normal"),
                                           (300, 3000, 700, 40, "uniform_pm1")])
