@@ -835,8 +835,8 @@ hipError_t launch_train(const X3Args& a, int grid, hipStream_t stream) {
 
 // Offsets into B are 32-bit; row-major B is read up to 64 rows past F.
 bool x3_sizes_ok(int64_t F, int64_t D, int64_t K, bool raw) {
-  if (cdiv(K, 32) > 4 || F > (1 << 20) || D > (1 << 22)) return false;
-  if (raw) return F * D * 4 < ((int64_t)1 << 31);
+  if (cdiv(K, 32) > 4 || F > (1 << 20)) return false;
+  if (raw) return D <= (1 << 22) && F * D * 4 < ((int64_t)1 << 31);
   return cdiv(D, 64) * 2 * cdiv(F, 8) * 1024 < ((int64_t)1 << 31);
 }
 
@@ -894,13 +894,14 @@ hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* 
                               N - p.head, K, p.ds, stream);
 }
 
-// Below about 1.5e8 multiply-adds a call is its start, which is 2-3 us longer
-// here (N = 256, F = 33, D = 512: 15.5 us against 13.1 us packed and 13.3 us
-// raw on the kernels for fp32 instructions; N = 300, F = 617, D = 10240: 53 us
-// against 76 and 129 us).
+// Not by N: a training set fed in chunks gets the signs, and so the counts, of one
+// call. Against the kernels for fp32 instructions the packed form is faster at all
+// sizes measured (N = 1 F = 4 D = 64 6.9 against 9.8 us, N = 60 F = 561 D = 2048 27
+// against 70, N = 1024 F = 561 D = 10240 89 against 243), the raw form above one
+// group of features (D = 2048: F = 16 N = 32 7.0 against 5.1 us, N = 65536 106 against
+// 105; F = 24 7.5 against 6.9 and 118 against 169; F = 100 N = 32 10.5 against 17.4).
 bool bundle_x3_ok(int64_t N, int64_t F, int64_t D, int64_t K, bool raw) {
-  return N >= 1 && N <= (1 << 30) && x3_sizes_ok(F, D, K, raw) &&
-         (double)N * (double)F * (double)D >= 1.5e8;
+  return N >= 1 && N <= (1 << 30) && x3_sizes_ok(F, D, K, raw) && (!raw || F > 16);
 }
 
 hipError_t launch_bundle_x3(const void* X, const void* B, bool raw, const int32_t* y,

@@ -262,6 +262,34 @@ def test_neighbours_do_not_matter(hd):
                                   b if what == "row" else b[:, cols]), (what, k)
 
 
+@pytest.mark.parametrize("N,F,D", [(1500, 561, 2048), (700, 21, 256), (3000, 600, 2816)])
+def test_training_in_chunks(hd, N, F, D):
+    """The counts of one call bit for bit, from chunks of all sizes, on sums
+    within rounding of zero (every row a multiple of one, the last row of B
+    cancels it): which sign such a sum takes depends on the kernel, so it must
+    not depend on the chunk."""
+    torch = torch_or_skip()
+    announce(f"x3 training in chunks N={N} F={F} D={D}")
+    K, g = 4, np.random.default_rng(N)
+    x = g.standard_normal(F).astype(np.float32)
+    x[-1] = 1.0
+    X = (x * 2.0 ** g.integers(-3, 4, (N, 1))).astype(np.float32)
+    B = g.standard_normal((F, D)).astype(np.float32)
+    B[-1] = -(x[:-1].astype(np.float64) @ B[:-1].astype(np.float64))
+    Xd, Bd = torch.from_numpy(X).cuda(), torch.from_numpy(B).cuda()
+    yd = torch.from_numpy(g.integers(0, K, N).astype(np.int32)).cuda()
+    m = hd.pack_model(Bd, K=K)
+    for call in (lambda *a, **k: hd.bundle_classes_packed(a[0], m, *a[1:], **k),
+                 lambda *a, **k: hd.bundle_classes(a[0], Bd, *a[1:], **k)):
+        one = call(Xd, yd, K)
+        for cuts in ((1, 60, 245), (33, 34, 161, 400), (N - 1,)):
+            counts = torch.zeros_like(one)
+            for a, b in zip((0,) + cuts, cuts + (N,)):
+                call(Xd[a:b], yd[a:b], K, counts=counts)
+            torch.cuda.synchronize()
+            assert torch.equal(one, counts), cuts
+
+
 @pytest.mark.parametrize("N,F,D,K,dist", [(512, 784, 2048, 10, "uniform01_zero20"),
                                           (512, 617, 1500, 26, "normal"),
                                           (300, 3000, 700, 40, "uniform_pm1")])
