@@ -13,8 +13,13 @@
 //
 // Rows that are not 4-byte aligned (odd F): rows n with the same n mod Q
 // (Q = 2 for bf16, up to 4 for int8) start at the same byte offset from a
-// dword, so a unit takes 32 rows of one such class, reads them from the dword
-// before, and B is loaded shifted by as many rows; no element is moved.
+// dword, so a unit takes 32 rows of one such class and reads them from the dword
+// before. For int8, whose sums are exact in any order, B is loaded shifted by as
+// many rows and no element is moved. For bf16 (SHIFT) each fragment is shifted on
+// its way from LDS to the matrix instruction, with the word after it, so that a
+// sample's sums are rounded alike wherever its row starts: in a chunk of a training
+// set its index, and X itself, can be odd (N = 65536, F = 617, K = 26:
+// 803 us, 791 with B shifted).
 //
 // Matrix-core bound, at the clock that dense matrix work leaves (about 1.8 GHz).
 // Against X staged through registers between barriers (bundle_mfma_kernel),
@@ -49,7 +54,7 @@ struct BregArgs {
   int N, F, D, K, ndb, ngroups;
 };
 
-template <class Tr, int NFS, int KB>
+template <class Tr, int NFS, int KB, bool SHIFT>
 __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
   constexpr int DP = ring_depth(NFS, KB);
   constexpr int P = NFS / kWaves + 1;  // loads per wave and unit (fragments, labels)
@@ -57,6 +62,7 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
   constexpr int MID = NFS / 2;
   constexpr int kOut = P * (R - 3);  // see large_fused_kernel_xreg
   constexpr int kSlot = slot_bytes(NFS);
+  static_assert(NFS % 2 == 0 && (!SHIFT || Tr::kEsz == 2), "shift");
   static_assert(NFS % DP == 0 && P <= NFS - MID && R >= 3 && kOut <= 63, "schedule");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -89,10 +95,11 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) cacc[b][kb][r] = 0;
 
-  const uint32_t sh = ((uint32_t)c * row_bytes) & 3u;  // bytes before the row in its first dword
+  // bytes before the row in its first dword
+  const uint32_t sh = ((uint32_t)(uintptr_t)a.X + (uint32_t)c * row_bytes) & 3u;
   const int nfx = (int)((row_bytes + sh + 31u) / 32u);  // f-steps of a shifted row
 
-  // B of this wave's columns as Stage I operands, shifted by sh bytes
+  // B of this wave's columns as Stage I operands (int8: shifted by sh bytes)
   uint4 bs[NFS][2];
   {
     const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
@@ -104,7 +111,7 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
         bs[s][b] = s < nfs ? __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                  brs, ((db + b) * nfs + s) * 1024 + lane * 16, 0, 0))
                            : make_uint4(0u, 0u, 0u, 0u);
-    if (sh != 0) {
+    if (Tr::kEsz == 1 && sh != 0) {
       // the word before a lane's rows is the last one of the other half of
       // the wave: of this f-step (upper half) or of the one before
       const uint32_t k = 4u - sh;
@@ -136,13 +143,12 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
       asm volatile("" : "+a"(t));
       bs[s][b] = __builtin_bit_cast(uint4, t);
     }
-  // bf16: what the first and the last f-step hold of other rows is cleared
-  // (it meets zero rows of B, but may be infinite or NaN)
-  uint32_t mfirst = 0xffffffffu, mlast[4];
-  if (half == 0 && sh == 2) mfirst = 0xffff0000u;
+  // bf16: what the last f-step holds past the row is cleared (it meets zero rows of
+  // B, but may be infinite or NaN)
+  uint32_t mlast[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int k = (int)(row_bytes + sh) - (nfx - 1) * 32 - half * 16 - 4 * q;
+    const int k = (int)row_bytes - (nfs - 1) * 32 - half * 16 - 4 * q;
     mlast[q] = k >= 4 ? 0xffffffffu : k <= 0 ? 0u : 0xffffffffu >> (8 * (4 - k));
   }
 
@@ -173,14 +179,29 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
 
   const unsigned char* frag = lds + lane * 16;
   uint4 ring[DP];
+  // SHIFT: the word after a lane's 16 bytes is 512 bytes on in LDS in either half of
+  // the wave (the other half's of this f-step, or of the next one), read two steps
+  // ahead. Past the last f-step it is not the row's, as are the f-steps past nfs.
+  uint32_t after[2];
+  auto word_after = [&](const unsigned char* f) {
+    return *reinterpret_cast<const uint32_t*>(f + 512);
+  };
   auto clean = [&](uint4 v, int s) -> uint4 {
+    if constexpr (SHIFT)
+      v = make_uint4(__builtin_amdgcn_alignbyte(v.y, v.x, sh),
+                     __builtin_amdgcn_alignbyte(v.z, v.y, sh),
+                     __builtin_amdgcn_alignbyte(v.w, v.z, sh),
+                     __builtin_amdgcn_alignbyte(after[s % 2], v.w, sh));
     if constexpr (Tr::kEsz == 2) {
-      if (s == 0) v.x &= mfirst;
-      if (s >= (NFS > 8 ? NFS - 4 : 0) && s == nfx - 1) {
-        v.x &= mlast[0];
-        v.y &= mlast[1];
-        v.z &= mlast[2];
-        v.w &= mlast[3];
+      if (s >= (NFS > 8 ? NFS - 4 : 0)) {
+        if (s == nfs - 1) {
+          v.x &= mlast[0];
+          v.y &= mlast[1];
+          v.z &= mlast[2];
+          v.w &= mlast[3];
+        } else if (SHIFT && s >= nfs) {
+          v.w = 0u;
+        }
       }
     }
     return v;
@@ -188,6 +209,10 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
   for (int i = 0; i < DP; ++i) ring[i] = *reinterpret_cast<const uint4*>(frag + i * 1024);
+  if constexpr (SHIFT) {
+    after[0] = word_after(frag);
+    after[1] = word_after(frag + 1024);
+  }
 
   // HardSign of sums 4 q .. 4 q + 3 of a tile as +-1 bytes, a word of the B
   // operand of the class sums
@@ -253,6 +278,8 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kOut) : "memory");
       if (s >= MID && s - MID < P) issue(u + R - 1, slp, s - MID);
       const uint4 x = clean(ring[s % DP], s);
+      if constexpr (SHIFT)
+        after[s % 2] = word_after(s + 2 < NFS ? fr + (s + 2) * 1024 : fn + (s + 2 - NFS) * 1024);
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         if (s == 0)
@@ -270,7 +297,7 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, SHIFT ? 2 : 1, 0);
     }
   };
   auto tail = [&](const f32x16 (&pv)[2], int u, int slp) __attribute__((always_inline)) {
@@ -325,15 +352,17 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
   }
 }
 
-template <class Tr, int NFS, int KB>
+template <class Tr, int NFS, int KB, bool SHIFT>
 __global__ __launch_bounds__(kThreads, 1) void bundle_mfma_kernel_breg(BregArgs a) {
-  bundle_breg<Tr, NFS, KB>(a);
+  bundle_breg<Tr, NFS, KB, SHIFT>(a);
 }
 
-template <class Tr, int NFS, int KB>
+template <class Tr, int NFS, int KB, bool SHIFT>
 hipError_t launch_breg_t(const BregArgs& a, int grid, hipStream_t stream) {
-  constexpr size_t lds = (size_t)slots(NFS) * slot_bytes(NFS);
-  auto* k = &bundle_mfma_kernel_breg<Tr, NFS, KB>;
+  // (SHIFT reads up to 256 bytes past the last slot's labels)
+  constexpr size_t lds = (size_t)slots(NFS) * slot_bytes(NFS) + (SHIFT ? 256 : 0);
+  static_assert(lds <= 160 * 1024, "LDS");
+  auto* k = &bundle_mfma_kernel_breg<Tr, NFS, KB, SHIFT>;
   static PerDeviceOnce once;
   const hipError_t attr = once_per_device(once, [&] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(k),
@@ -344,26 +373,29 @@ hipError_t launch_breg_t(const BregArgs& a, int grid, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <class Tr, int KB, int NFS = 8>
+template <class Tr, int KB, bool SHIFT, int NFS = 8>
 hipError_t launch_breg_steps(int steps, const BregArgs& a, int grid, hipStream_t stream) {
   if constexpr (NFS <= max_steps(KB)) {
-    if (steps <= NFS) return launch_breg_t<Tr, NFS, KB>(a, grid, stream);
-    return launch_breg_steps<Tr, KB, NFS + 4>(steps, a, grid, stream);
+    if (steps <= NFS) return launch_breg_t<Tr, NFS, KB, SHIFT>(a, grid, stream);
+    return launch_breg_steps<Tr, KB, SHIFT, NFS + 4>(steps, a, grid, stream);
   }
   return hipErrorInvalidValue;
 }
 
-template <class Tr>
+template <class Tr, bool SHIFT>
 hipError_t launch_breg_tr(int steps, int kb, const BregArgs& a, int grid, hipStream_t stream) {
-  if (kb == 1) return launch_breg_steps<Tr, 1>(steps, a, grid, stream);
-  if (kb == 2) return launch_breg_steps<Tr, 2>(steps, a, grid, stream);
-  return launch_breg_steps<Tr, 4>(steps, a, grid, stream);
+  if (kb == 1) return launch_breg_steps<Tr, 1, SHIFT>(steps, a, grid, stream);
+  if (kb == 2) return launch_breg_steps<Tr, 2, SHIFT>(steps, a, grid, stream);
+  return launch_breg_steps<Tr, 4, SHIFT>(steps, a, grid, stream);
 }
 
 }  // namespace
 
+// X 4-byte aligned, or bf16 rows of odd length: those start at either offset anyway,
+// and a chunk from an odd row on must not take another kernel than the whole.
 bool bundle_breg_ok(const void* X, int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
-  if (dt == 0 || (uintptr_t)X % 4 != 0 || cdiv(K, 32) > 4) return false;
+  if (dt == 0 || cdiv(K, 32) > 4) return false;
+  if ((uintptr_t)X % 4 != 0 && !(dt == 1 && F % 2 != 0)) return false;
   const int64_t esz = dt == 1 ? 2 : 1, rb = F * esz;
   const int64_t maxsh = rb % 4 == 0 ? 0 : rb % 2 == 0 ? 2 : 3;
   return cdiv(rb + maxsh, 32) <= max_steps(kb_of(K)) && N <= (1 << 30) && D <= (1 << 29);
@@ -393,8 +425,9 @@ hipError_t launch_bundle_breg(const void* X, const void* packed, const int32_t* 
   BregArgs a{X, (const uint4*)packed, y, counts, (int)N, (int)F, (int)D, (int)K,
              (int)(cdiv(D, 64) * 2), (int)ngroups};
   const int grid = (int)(ncg * ngroups);
-  return dt == 1 ? launch_breg_tr<TrBF16>(steps, kb_of(K), a, grid, stream)
-                 : launch_breg_tr<TrI8>(steps, kb_of(K), a, grid, stream);
+  if (dt == 2) return launch_breg_tr<TrI8, false>(steps, kb_of(K), a, grid, stream);
+  return Q == 1 ? launch_breg_tr<TrBF16, false>(steps, kb_of(K), a, grid, stream)
+                : launch_breg_tr<TrBF16, true>(steps, kb_of(K), a, grid, stream);
 }
 
 }  // namespace hd

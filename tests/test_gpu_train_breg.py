@@ -98,3 +98,37 @@ def test_infinite_and_nan_features(hd, F):
     B[F - 1] = np.where(B[F - 1] == 0, 1, B[F - 1])
     y = labels(N, K, 6)
     assert np.array_equal(run(hd, X, B, y, K, "bf16"), oracle.bundle(X, B, y, K)["counts"])
+
+
+@pytest.mark.parametrize("N,F,D", [(130, 51, 2048), (700, 617, 1000), (300, 5, 300), (300, 255, 512)])
+def test_odd_rows_in_chunks(hd, N, F, D):
+    """bf16 rows of odd length: the counts of one call bit for bit, from chunks
+    that start at odd rows and from an X that starts inside a dword, on sums within
+    rounding of zero (every row a multiple of one; the last three rows of B, at X = 1,
+    cancel it to fp32's precision)."""
+    torch = torch_or_skip()
+    announce(f"breg odd rows in chunks N={N} F={F} D={D}")
+    K, g = 4, np.random.default_rng(N + F)
+    bf = lambda a: torch.from_numpy(a.astype(np.float32)).to(torch.bfloat16)
+    x, B = bf(g.standard_normal(F)), bf(g.standard_normal((F, D)))
+    x[-3:] = 1.0
+    left = -(x[:-3].double() @ B[:-3].double())
+    for i in range(3):
+        B[F - 3 + i] = left.to(torch.bfloat16)
+        left = left - B[F - 3 + i].double()
+    X = (x.float() * torch.from_numpy(2.0 ** g.integers(-3, 4, (N, 1))).float()).to(torch.bfloat16)
+    Xd = X.cuda()
+    m = hd.pack_model(B.cuda(), K=K)
+    yd = torch.from_numpy(g.integers(0, K, N).astype(np.int32)).cuda()
+    one = hd.bundle_classes_packed(Xd, m, yd, K)
+    for cuts in ((1, 60), (33, 34, 101), (N - 1,)):
+        counts = torch.zeros_like(one)
+        for a, b in zip((0,) + cuts, cuts + (N,)):
+            hd.bundle_classes_packed(Xd[a:b], m, yd[a:b], K, counts=counts)
+        torch.cuda.synchronize()
+        assert torch.equal(one, counts), cuts
+    buf = torch.zeros(N * F + 1, dtype=torch.bfloat16, device="cuda")
+    buf[1:] = Xd.reshape(-1)
+    shifted = hd.bundle_classes_packed(buf[1:].view(N, F), m, yd, K)
+    torch.cuda.synchronize()
+    assert torch.equal(one, shifted)
