@@ -268,12 +268,15 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
   // The plan taken for this X (its alignment can change the tile size and the
   // D split) must fit the workspace the caller sized with the query.
   const size_t plan_ws = hd::large_workspace_bytes_for(N, F, D, K, dt, (uintptr_t)X % 16 == 0);
+  // Workspace that the split of D is chosen by, and so the order of its sums: in
+  // the deterministic mode what every call has, not what this one brings.
+  const size_t least = hd::large_workspace_min(N, F, D, K, dt);
   if (packed) {
     if (workspace_bytes < plan_ws) return HD_ERR_WORKSPACE;
     if (dry) return HD_OK;
     return from_hip(
         hd::launch_large(X, packed, labels, scores, N, F, D, K, dt, act, workspace,
-                         workspace_bytes, stream));
+                         det ? least : workspace_bytes, stream));
   }
   // Raw matrices: the scratch that must start at zero (tile counters, split-D
   // partial scores) stays at offset 0, the same place every route keeps it, and
@@ -283,17 +286,18 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
   // (the fastest plan's scratch when the workspace has room for it)
   size_t zone = align256(hd::large_workspace_bytes(N, F, D, K, dt));
   const size_t pb = hd::large_packed_bytes(F, D, K, dt);
-  if (workspace_bytes < zone + pb) zone = align256(hd::large_workspace_min(N, F, D, K, dt));
+  if (workspace_bytes < zone + pb) zone = align256(least);
   if (plan_ws > zone || workspace_bytes < zone + pb) return HD_ERR_WORKSPACE;
   if (dry) return HD_OK;
   hipError_t err = hipSuccess;
-  if (hd::launch_large_raw(X, B, C, labels, scores, N, F, D, K, dt, act, workspace, zone, stream,
+  const size_t cap = det ? least : zone;
+  if (hd::launch_large_raw(X, B, C, labels, scores, N, F, D, K, dt, act, workspace, cap, stream,
                            &err))
     return from_hip(err);
   char* copy = static_cast<char*>(workspace) + zone;
   if (hd::launch_pack(B, C, F, D, K, dt, copy, stream) != hipSuccess) return HD_ERR_HIP;
   const hipError_t e =
-      hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace, zone, stream);
+      hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace, cap, stream);
   if (e != hipSuccess) return HD_ERR_HIP;
   return from_hip(hd::launch_zero(copy, pb, stream));
 }

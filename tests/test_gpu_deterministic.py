@@ -100,3 +100,56 @@ def test_deterministic_noalloc(hd):
         torch.cuda.synchronize()
         assert torch.equal(S2, S0) and torch.equal(y2, y0)
     assert torch.equal(S1, S0) and torch.equal(y1, y0)
+
+
+# The split of D of the large-batch kernels follows the workspace, in the default
+# mode; two 64-sample calls or one of 128 likewise.
+@pytest.mark.parametrize("N,F,D,K,dtype", [(4096, 617, 10240, 26, "bf16"),
+                                           (300, 784, 10240, 10, "bf16"),
+                                           (2500, 300, 10240, 20, "f32"),
+                                           (900, 1500, 4096, 40, "f32"),
+                                           (100, 561, 10240, 6, "bf16"),
+                                           (250, 300, 5000, 10, "bf16")])
+def test_deterministic_whatever_the_workspace(hd, N, F, D, K, dtype):
+    """The same bits from the least workspace that a call takes, the size
+    query's, a larger one and the library's own scratch."""
+    torch = torch_or_skip()
+    announce(f"deterministic workspaces {dtype} N={N} F={F} D={D} K={K}")
+    X, B, C = hd_inputs.make_inputs(N, F, D, K, "uniform_pm1", seed=N, dtype=dtype)
+    Xd, Bd, Cd = dev(X, dtype), dev(B, dtype), dev(C, dtype)
+    m = hd.pack_model(Bd, Cd)
+    out = (torch.empty(N, dtype=torch.int32, device="cuda"),
+           torch.empty((N, K), dtype=torch.float32, device="cuda"))
+
+    def call(ws, raw):
+        a = (Xd, Bd, Cd) if raw else (Xd, m)
+        (hd.infer if raw else hd.infer_packed)(*a, out=out, workspace=ws, deterministic=True)
+        torch.cuda.synchronize()
+        return out[0].clone(), out[1].clone()
+
+    for raw in (False, True):
+        L = hd.lib()
+        query = L.hd_infer_workspace_bytes if raw else L.hd_infer_packed_workspace_bytes
+        full = int(query(N, F, D, K, m.dt))
+        ws = torch.zeros(2 * full + 256, dtype=torch.uint8, device="cuda")
+        want = call(ws[:full], raw)
+        lo, hi = 0, full  # the least size: below it the call is refused
+        while hi - lo > 256:
+            mid = (lo + hi) // 2 // 256 * 256
+            try:
+                call(ws[:mid], raw)
+                hi = mid
+            except hd.HDError as e:
+                assert e.status == hd.HD_ERR_WORKSPACE
+                lo = mid
+        for nbytes in (hi, (hi + full) // 2, 2 * full):
+            got = call(ws[:nbytes], raw)
+            assert torch.equal(got[1], want[1]) and torch.equal(got[0], want[0]), (raw, nbytes)
+        if not raw:
+            try:
+                got = hd.infer_packed_noalloc(Xd, m, return_scores=True, deterministic=True)
+            except hd.HDError as e:  # more than the scratch at least
+                assert e.status == hd.HD_ERR_WORKSPACE
+                continue
+            torch.cuda.synchronize()
+            assert torch.equal(got[1], want[1]) and torch.equal(got[0], want[0])
