@@ -281,8 +281,7 @@ hd_status hd_bundle_classes_packed(const void *X, const void *packed, const int3
  * Introspection: the name of the kernel that hd_bundle_classes (packed == 0)
  * or hd_bundle_classes_packed (packed != 0) launches for these sizes,
  * assuming a 16-byte aligned X; "" when the call would be rejected. Static
- * string. Packed bf16 and int8 calls are named by how X's rows are aligned;
- * those with rows of at most 40 16-byte pairs run bundle_mfma_kernel_breg.
+ * string.
  */
 const char *hd_bundle_kernel(int64_t N, int64_t F, int64_t D, int64_t K, hd_dtype dt, int packed);
 

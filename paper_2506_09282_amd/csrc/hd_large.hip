@@ -1593,14 +1593,11 @@ bool bundle_packed_supported(int64_t N, int64_t F, int64_t D, int64_t K, int dt)
 }
 
 const char* bundle_packed_kernel_name(int64_t N, int64_t F, int64_t D, int64_t K, int dt) {
-  if (dt == 0) return bundle_cfg<TrF32>(N, F, D, K).ok ? "bundle_mfma_kernel" : "";
-  if (dt == 2) {
-    const BundleCfg c = bundle_cfg<TrI8>(N, F, D, K);
-    if (!c.ok) return "";
-    return c.dma_upw > 0 ? "bundle_dma_kernel" : "bundle_mfma_kernel";
-  }
-  const BundleCfg c = bundle_cfg<TrBF16>(N, F, D, K);
+  const BundleCfg c =
+      with_traits(dt, [&](auto tr) { return bundle_cfg<decltype(tr)>(N, F, D, K); });
   if (!c.ok) return "";
+  if (dt == 0 && bundle_x3_ok(N, F, D, K, false)) return "bundle_mfma_kernel_x3";
+  if (bundle_breg_ok(nullptr, N, F, D, K, dt)) return "bundle_mfma_kernel_breg";
   return c.dma_upw > 0 ? "bundle_dma_kernel" : "bundle_mfma_kernel";
 }
 
@@ -1658,6 +1655,9 @@ const char* large_kernel_name(int64_t N, int64_t F, int64_t D, int64_t K, int dt
   const LargeCfg c =
       with_traits(dt, [&](auto tr) { return large_cfg<decltype(tr)>(N, F, D, K); });
   if (!c.ok) return "";
+  if (dt == 0 ? x3_plan(N, F, D, K, 0, false, ~size_t(0)).ok
+              : xreg_plan(N, F, D, K, dt, 0, true, ~size_t(0)).ok)
+    return dt == 0 ? "large_fused_kernel_x3" : "large_fused_kernel_xreg";
   if (c.fsc > 0) return c.dma ? "large_chunked_dma_kernel" : "large_chunked_kernel";
   return "large_fused_kernel";
 }

@@ -125,7 +125,7 @@ bool bundle_supported(int64_t K) { return K >= 1 && K <= kBundleMaxK; }
 hipError_t launch_bundle(const void* X, const void* B, const int32_t* y, int32_t* counts,
                          int64_t N, int64_t F, int64_t D, int64_t K, int dt,
                          hipStream_t stream) {
-  if (dt == 0 && K <= kBundleMfmaMaxK && bundle_x3_ok(N, F, D, K, true))
+  if (dt == 0 && bundle_x3_ok(N, F, D, K, true))
     return launch_bundle_x3(X, B, true, y, counts, N, F, D, K, stream);
   const int64_t dblocks = cdiv(D, kTile), ntiles = cdiv(N, kTile);
   // enough workgroups to fill the chip (several per compute unit), each

@@ -202,10 +202,10 @@ def test_int8_limits(L):
     # 64 < N <= 256: 64-sample calls of the fragment kernel; above, the large kernels
     assert L.hd_infer_kernel(65, 561, 10240, 6, I8, 1) == b"small_frag_mfma_kernel"
     assert L.hd_infer_kernel(256, 561, 10240, 6, I8, 1) == b"small_frag_mfma_kernel"
-    assert L.hd_infer_kernel(257, 561, 10240, 6, I8, 1) == b"large_fused_kernel"
-    assert L.hd_infer_kernel(32, 561, 10240, 6, I8, 0) == b"large_fused_kernel"  # raw B, C
+    assert L.hd_infer_kernel(257, 561, 10240, 6, I8, 1) == b"large_fused_kernel_xreg"
+    assert L.hd_infer_kernel(32, 561, 10240, 6, I8, 0) == b"large_fused_kernel_xreg"  # raw B, C
     assert L.hd_infer_kernel(32, 1025, 10240, 6, I8, 1) != b"small_frag_mfma_kernel"
-    assert L.hd_infer_kernel(32, 561, 10240, 17, I8, 1) == b"large_fused_kernel"
+    assert L.hd_infer_kernel(32, 561, 10240, 17, I8, 1) == b"large_fused_kernel_xreg"
     # (an X that is not 16-byte aligned falls back to the large-batch kernels,
     # and the workspace query covers that route: tests/test_gpu_int8.py)
     assert L.hd_infer_kernel(1, 131071, 64, 2, I8, 1) == b"large_chunked_kernel"
@@ -214,7 +214,7 @@ def test_int8_limits(L):
     assert L.hd_bundle_classes(FAKE, FAKE, FAKE, FAKE, 4, 8, 64, 3, I8, None) == \
         hd.HD_ERR_UNSUPPORTED
     assert L.hd_infer_stream_workspace_bytes(4, 1, 561, 10240, 6, I8) == 0
-    assert L.hd_bundle_kernel(100, 617, 4096, 26, I8, 1) == b"bundle_mfma_kernel"
+    assert L.hd_bundle_kernel(100, 617, 4096, 26, I8, 1) == b"bundle_mfma_kernel_breg"
     assert L.hd_bundle_kernel(100, 617, 4096, 26, I8, 0) == b""
     # the packed image's small-batch section holds C's column tiles and the
     # fragment copy of B (F <= 1024), not B's column tiles
@@ -247,17 +247,17 @@ def test_routes_of_new_paths(L):
     k = L.hd_infer_kernel
     # packed bf16 small batches: the fragment kernel (bf16 fragments); raw: large-batch
     assert k(32, 561, 10240, 6, hd.HD_BF16, 1) == b"small_frag_mfma_kernel"
-    assert k(32, 561, 10240, 6, hd.HD_BF16, 0) == b"large_fused_kernel"
-    assert k(32, 561, 10240, 17, hd.HD_BF16, 1) == b"large_fused_kernel"  # K > 16
+    assert k(32, 561, 10240, 6, hd.HD_BF16, 0) == b"large_fused_kernel_xreg"
+    assert k(32, 561, 10240, 17, hd.HD_BF16, 1) == b"large_fused_kernel_xreg"  # K > 16
     # 64-sample calls of the fragment kernel up to 256 samples of a packed bf16 model
     assert k(256, 561, 10240, 6, hd.HD_BF16, 1) == b"small_frag_mfma_kernel"
-    assert k(257, 561, 10240, 6, hd.HD_BF16, 1) == b"large_fused_kernel"
-    assert k(100, 561, 10240, 6, hd.HD_BF16, 0) == b"large_fused_kernel"
+    assert k(257, 561, 10240, 6, hd.HD_BF16, 1) == b"large_fused_kernel_xreg"
+    assert k(100, 561, 10240, 6, hd.HD_BF16, 0) == b"large_fused_kernel_xreg"
     b = L.hd_bundle_kernel
     assert b(16384, 3072, 10240, 10, hd.HD_BF16, 1) == b"bundle_dma_kernel"
     assert b(16384, 3072, 10240, 10, hd.HD_I8, 1) == b"bundle_dma_kernel"
     assert b(16384, 3071, 10240, 10, hd.HD_BF16, 1) == b"bundle_mfma_kernel"  # F % 8 != 0
-    assert b(4096, 784, 10240, 10, hd.HD_F32, 1) == b"bundle_mfma_kernel"
+    assert b(4096, 784, 10240, 10, hd.HD_F32, 1) == b"bundle_mfma_kernel_x3"
     assert b(4096, 784, 10240, 129, hd.HD_F32, 1) == b""      # packed path: K <= 128
     assert b(4096, 784, 10240, 512, hd.HD_F32, 0) == b"bundle_valu_kernel"
     assert b(4096, 784, 10240, 513, hd.HD_F32, 0) == b""

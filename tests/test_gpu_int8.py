@@ -49,11 +49,14 @@ def check(y, S, ref):
 # (double-buffered by buffer-to-LDS loads when F is a multiple of 16, through
 # registers when ragged), one sample (split of D), ragged D.
 CASES = [
-    (300, 617, 4096, 26, True, "large_fused_kernel"),
-    (300, 617, 4096, 26, False, "large_fused_kernel"),
+    (300, 617, 4096, 26, True, "large_fused_kernel_xreg"),
+    (300, 617, 4096, 26, False, "large_fused_kernel_xreg"),
     (1, 561, 10240, 6, False, "large_fused_kernel"),
-    (129, 300, 2000, 100, True, "large_fused_kernel"),
-    (77, 1000, 999, 40, False, "large_fused_kernel"),
+    (129, 300, 2000, 100, True, "large_fused_kernel_xreg"),
+    (77, 1000, 999, 40, False, "large_fused_kernel_xreg"),
+    (300, 1570, 4096, 26, True, "large_fused_kernel"),
+    (129, 700, 2000, 100, True, "large_fused_kernel"),
+    (77, 1100, 999, 40, False, "large_fused_kernel"),
     (200, 3001, 1024, 10, True, "large_fused_kernel"),
     (200, 3072, 1024, 10, True, "large_chunked_dma_kernel"),
     (1000, 4096, 2048, 20, True, "large_chunked_dma_kernel"),
@@ -160,7 +163,8 @@ def test_int8_small_unaligned_x_and_noalloc(hd):
         check(y.cpu().numpy(), S.cpu().numpy().astype(np.float64), r)
 
 
-@pytest.mark.parametrize("N,F,kernel", [(300, 40, "large_fused_kernel"),
+@pytest.mark.parametrize("N,F,kernel", [(300, 40, "large_fused_kernel_xreg"),
+                                        (300, 2000, "large_fused_kernel"),
                                         (100, 6000, "large_chunked_dma_kernel"),
                                         (100, 6001, "large_chunked_kernel")])
 def test_int8_zero_sums_and_argmax_ties(hd, N, F, kernel):
@@ -204,7 +208,8 @@ def test_int8_largest_d(hd):
     check(y, S, oracle.infer(X, B, C))
 
 
-@pytest.mark.parametrize("N,F,D,K,kernel", [(2000, 617, 4096, 26, "bundle_mfma_kernel"),
+@pytest.mark.parametrize("N,F,D,K,kernel", [(2000, 617, 4096, 26, "bundle_mfma_kernel_breg"),
+                                             (2000, 1301, 4096, 26, "bundle_mfma_kernel"),
                                              (1500, 3072, 2000, 26, "bundle_dma_kernel"),
                                              (130, 4096, 700, 60, "bundle_dma_kernel")])
 def test_int8_training_and_round_trip(hd, N, F, D, K, kernel):

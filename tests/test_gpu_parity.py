@@ -101,7 +101,8 @@ def test_colour_workload_sampled(hd, name, dtype):
     torch = torch_or_skip()
     w = hd_inputs.WORKLOADS[name]
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    assert hd.infer_kernel(w.N, w.F, w.D, w.K, tdt).startswith("large_chunked")
+    assert hd.infer_kernel(w.N, w.F, w.D, w.K, tdt) == (
+        "large_chunked_dma_kernel" if dtype == "bf16" else "large_fused_kernel_x3")
     announce(f"{name} {dtype} N={w.N} F={w.F}")
     X, B, C = inputs(w.N, w.F, w.D, w.K, w.x_dist, dtype=dtype)
     y, S = run(hd, X, B, C, dtype, packed=True)
@@ -152,7 +153,8 @@ def test_colour_single_sample_d_sweep_ends(hd, D, dtype):
 # --- wide features: the X tile streamed through LDS in chunks ---------------
 
 # (N, F, D, K, dtype, kernel): bf16 with F % 8 == 0 double-buffers the chunks
-# through buffer-to-LDS loads; ragged F and fp32 stage them through registers.
+# through buffer-to-LDS loads; ragged F stages them through registers; fp32 runs
+# on the split kernel, which takes any F.
 CHUNKED = [(200, 3000, 300, 10, "bf16", "dma"), (130, 2999, 200, 7, "bf16", ""),
            (70, 2600, 130, 100, "bf16", "dma"), (150, 1300, 256, 5, "f32", ""),
            (90, 1283, 200, 40, "f32", ""), (65, 1500, 100, 70, "f32", ""),
@@ -165,7 +167,8 @@ CHUNKED = [(200, 3000, 300, 10, "bf16", "dma"), (130, 2999, 200, 7, "bf16", ""),
 def test_wide_features_chunked(hd, N, F, D, K, dtype, kind):
     torch = torch_or_skip()
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    want = "large_chunked_dma_kernel" if kind == "dma" else "large_chunked_kernel"
+    want = ("large_chunked_dma_kernel" if kind == "dma" else
+            "large_fused_kernel_x3" if dtype == "f32" else "large_chunked_kernel")
     assert hd.infer_kernel(N, F, D, K, tdt) == want
     announce(f"chunked {dtype} N={N} F={F} D={D} K={K}")
     X, B, C = inputs(N, F, D, K, "normal", seed=F + K, dtype=dtype)
@@ -226,15 +229,20 @@ INTEGER = [
     (64, 561, 20480, 6, "f32", True, "small_mfma_kernel"),
     (64, 100, 2048, 17, "f32", False, "small_mfma_kernel"),
     (65, 100, 2048, 17, "f32", False, None),
-    (300, 617, 4096, 26, "f32", False, "large_fused_kernel"),
-    (300, 617, 4096, 26, "bf16", True, "large_fused_kernel"),
-    (257, 31, 700, 3, "bf16", False, "large_fused_kernel"),
-    (300, 784, 2048, 10, "bf16", True, "large_fused_kernel"),
+    (300, 617, 4096, 26, "f32", False, "large_fused_kernel_x3"),
+    (300, 617, 4096, 26, "bf16", True, "large_fused_kernel_xreg"),
+    (257, 31, 700, 3, "bf16", False, "large_fused_kernel_xreg"),
+    (300, 784, 2048, 10, "bf16", True, "large_fused_kernel_xreg"),
+    # rows beyond the kernel with X in registers: four, two and one sample tiles
+    (300, 785, 2048, 10, "bf16", True, "large_fused_kernel"),
+    (257, 600, 700, 64, "bf16", False, "large_fused_kernel"),
+    (129, 401, 4096, 128, "bf16", True, "large_fused_kernel"),
+    (300, 2001, 500, 10, "bf16", True, "large_fused_kernel"),
     (32, 561, 2048, 6, "bf16", True, "small_frag_mfma_kernel"),
     (16, 561, 10240, 6, "bf16", True, "small_frag_mfma_kernel"),
     (40, 301, 1000, 16, "bf16", True, "small_frag_mfma_kernel"),
     (60, 1000, 1500, 5, "bf16", True, "small_frag_mfma_kernel"),  # two sample passes
-    (32, 561, 2048, 17, "bf16", True, "large_fused_kernel"),
+    (32, 561, 2048, 17, "bf16", True, "large_fused_kernel_xreg"),
     (128, 561, 2048, 6, "bf16", True, "small_frag_mfma_kernel"),  # two 64-sample calls
     (250, 561, 2048, 6, "bf16", True, "small_frag_mfma_kernel"),  # four calls, the last ragged
     (4, 561, 2048, 6, "bf16", True, "small_flat_kernel"),
@@ -243,7 +251,7 @@ INTEGER = [
     (8, 561, 10240, 6, "f32", True, "small_frag_mfma_kernel"),
     (200, 3072, 1024, 10, "bf16", True, "large_chunked_dma_kernel"),
     (130, 2600, 512, 100, "bf16", False, "large_chunked_dma_kernel"),
-    (200, 3072, 1024, 10, "f32", True, "large_chunked_kernel"),
+    (200, 3072, 1024, 10, "f32", True, "large_fused_kernel_x3"),
     (150, 2999, 700, 5, "bf16", True, "large_chunked_kernel"),
 ]
 
@@ -267,17 +275,19 @@ def test_integer_inputs_bit_exact(hd, N, F, D, K, dtype, packed, kernel):
 TIES = [
     (5, 40, 512, "f32", False, "small_flat_kernel"),
     (200, 40, 512, "f32", False, "small_mfma_kernel"),
-    (300, 40, 512, "f32", False, "large_fused_kernel"),
-    (300, 700, 512, "bf16", True, "large_fused_kernel"),
+    (300, 40, 512, "f32", False, "large_fused_kernel_x3"),
+    (300, 700, 512, "bf16", True, "large_fused_kernel_xreg"),
+    (300, 1000, 512, "bf16", True, "large_fused_kernel"),
     (250, 700, 512, "bf16", True, "small_frag_mfma_kernel"),  # four 64-sample calls
     (5, 40, 512, "bf16", False, "small_flat_kernel"),
-    (200, 40, 512, "bf16", False, "large_fused_kernel"),
+    (200, 40, 512, "bf16", False, "large_fused_kernel_xreg"),
+    (9, 40, 512, "bf16", False, "large_fused_kernel"),
     (32, 40, 512, "f32", True, "small_frag_mfma_kernel"),
     (64, 700, 4096, "f32", True, "small_frag_mfma_kernel"),  # two sample passes
     (64, 200, 1024, "f32", True, "small_frag_mfma_kernel"),
     (100, 2560, 512, "bf16", True, "large_chunked_dma_kernel"),
     (32, 40, 512, "bf16", True, "small_frag_mfma_kernel"),
-    (100, 2560, 512, "f32", True, "large_chunked_kernel"),
+    (100, 2560, 512, "f32", True, "large_fused_kernel_x3"),
     (100, 2561, 512, "bf16", False, "large_chunked_kernel"),
 ]
 

@@ -121,17 +121,23 @@ def test_integer_counts_bit_exact(hd, N, F, D, K, spill, dtype, path):
 # Every training kernel on integer inputs, asserting which one ran:
 # (N, F, D, K, dtype, path, kernel).
 KERNELS = [
-    (700, 100, 1000, 9, "f32", "raw", "bundle_valu_kernel"),
+    (700, 100, 1000, 9, "f32", "raw", "bundle_mfma_kernel_x3"),
     (700, 100, 1000, 9, "bf16", "raw", "bundle_valu_kernel"),
-    (700, 100, 1000, 9, "f32", "packed", "bundle_mfma_kernel"),
-    (3000, 2999, 700, 100, "f32", "packed", "bundle_mfma_kernel"),
-    (700, 101, 1000, 9, "bf16", "packed", "bundle_mfma_kernel"),
+    (700, 100, 1000, 9, "f32", "packed", "bundle_mfma_kernel_x3"),
+    (3000, 2999, 700, 100, "f32", "packed", "bundle_mfma_kernel_x3"),
+    (700, 101, 1000, 9, "bf16", "packed", "bundle_mfma_kernel_breg"),
     (130, 3072, 1024, 100, "bf16", "packed", "bundle_mfma_kernel"),
     (1000, 3072, 2048, 10, "bf16", "packed", "bundle_dma_kernel"),
     (1, 3072, 2048, 10, "bf16", "packed", "bundle_dma_kernel"),
-    (65, 256, 10240, 26, "bf16", "packed", "bundle_dma_kernel"),
+    (65, 256, 10240, 26, "bf16", "packed", "bundle_mfma_kernel_breg"),
     (2047, 616, 1000, 60, "bf16", "packed", "bundle_dma_kernel"),
-    (333, 8, 64, 2, "bf16", "packed", "bundle_dma_kernel"),
+    (333, 8, 64, 2, "bf16", "packed", "bundle_mfma_kernel_breg"),
+    (700, 16, 1000, 9, "f32", "raw", "bundle_valu_kernel"),
+    (700, 101, 1000, 300, "f32", "raw", "bundle_valu_kernel"),
+    # rows of more than 40 f-steps (32 for K > 32)
+    (700, 701, 1000, 9, "bf16", "packed", "bundle_mfma_kernel"),
+    (65, 648, 10240, 26, "bf16", "packed", "bundle_dma_kernel"),
+    (333, 704, 64, 2, "bf16", "packed", "bundle_dma_kernel"),
 ]
 
 
