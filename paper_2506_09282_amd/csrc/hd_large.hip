@@ -28,10 +28,11 @@
 // DS slices whose partial scores a second launch combines in slice order
 // (reduce_slices_kernel).
 //
-// What still runs here: the identity mode, bf16 and int8 rows that the kernel
-// with X in registers does not take (more than 49 f-steps, X not 4-byte
-// aligned), and fp32 models of 2 GiB and more. The packing and the entry points
-// of the path are here too.
+// What still runs here: the identity mode, and bf16 and int8 calls that the kernels
+// with an operand in registers do not take (inference: more than 49 f-steps, X not
+// 4-byte aligned, up to 16 samples of one class block; training: more than 40). fp32
+// with HardSign runs in hd_large_x3.hip, training too. The packing and the entry
+// points of the path are here.
 #include <type_traits>
 
 #include "hd_large.hpp"
@@ -936,17 +937,13 @@ __device__ __forceinline__ void bundle_stage(typename Tr::elem* xt, const typena
         }
       }
       uint4* dst = reinterpret_cast<uint4*>(xt + r * pitch + s * Tr::kFStep);
-      if constexpr (Tr::kEsz != 4) {
-        dst[0] = w[j][0];
-        dst[1] = w[j][1];
-      } else {  // fp32: even features of the step first (lds_pos)
-        dst[0] = make_uint4(w[j][0].x, w[j][0].z, w[j][1].x, w[j][1].z);
-        dst[1] = make_uint4(w[j][0].y, w[j][0].w, w[j][1].y, w[j][1].w);
-      }
+      dst[0] = w[j][0];
+      dst[1] = w[j][1];
     }
   }
 }
 
+// bf16 and int8
 template <class Tr, int NTILES, int OCC>
 __global__ __launch_bounds__(kThreads, OCC) void bundle_mfma_kernel(
     const typename Tr::elem* __restrict__ X, const uint4* __restrict__ Bp,
@@ -1446,9 +1443,12 @@ template <class Tr, int NTILES, int KB>
 hipError_t launch_cfg(const LargeCfg& c, const void* X, const uint4* Bp, const uint4* Cp,
                       int32_t* labels, float* scores, int64_t N, int64_t F, int64_t K, int ndb,
                       int act, void* ws, hipStream_t stream) {
-  const hipError_t e =
-      act ? launch_act<Tr, NTILES, KB, 1>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream)
-          : launch_act<Tr, NTILES, KB, 0>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
+  // (fp32 with HardSign: the split kernel takes all sizes that large_cfg does)
+  hipError_t e = hipErrorInvalidValue;
+  if (act)
+    e = launch_act<Tr, NTILES, KB, 1>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
+  else if constexpr (Tr::kEsz <= 2)
+    e = launch_act<Tr, NTILES, KB, 0>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
   if (e != hipSuccess || c.ds == 1) return e;
   return launch_reduce_slices(ws, labels, scores, N, K, c.ds, stream);
 }
@@ -1534,7 +1534,7 @@ BundleCfg bundle_cfg(int64_t N, int64_t F, int64_t D, int64_t K, bool x16 = true
   const int pad = pad_of<Tr>();
   const size_t fixed = 16 + sizeof(int) * (32 * c.nt + (size_t)K * kBundleCols);
   const size_t per_row = (size_t)32 * c.nt * Tr::kEsz;  // bytes per LDS column of the tile
-  // Two workgroups per compute unit (fp32) while the class counters leave
+  // Two workgroups per compute unit (bf16) while the class counters leave
   // room for a chunk of at least 4 f-steps in half the LDS, else one.
   if (c.occ > 1 && fixed + per_row * (4 * Tr::kFStep + pad) > (size_t)kLdsBytes / c.occ) c.occ = 1;
   const size_t budget = (size_t)kLdsBytes / c.occ;
@@ -1609,17 +1609,8 @@ hipError_t launch_bundle_packed(const void* X, const void* packed, const int32_t
     return launch_bundle_x3(X, packed, false, y, counts, N, F, D, K, stream);
   if (bundle_breg_ok(X, N, F, D, K, dt))
     return launch_bundle_breg(X, packed, y, counts, N, F, D, K, dt, stream);
-  if (dt == 0) {
-    const BundleCfg c = bundle_cfg<TrF32>(N, F, D, K);
-    if (!c.ok) return hipErrorInvalidValue;
-    const PackGeom g = pack_geom<TrF32>(F, D, 1);
-    auto* k = &bundle_mfma_kernel<TrF32, 2, 2>;
-    const hipError_t a = allow_large_lds<&bundle_mfma_kernel<TrF32, 2, 2>>();
-    if (a != hipSuccess) return a;
-    hipLaunchKernelGGL(k, dim3((unsigned)(c.ncg * c.ngroups)), block, c.lds, stream,
-                       (const float*)X, (const uint4*)packed, y, counts, (int)N, (int)F, (int)D,
-                       (int)K, g.ndb, c.ngroups, c.fsc);
-  } else if (dt == 2) {
+  if (dt == 0) return hipErrorInvalidValue;  // (fp32: the split kernel takes all that is supported)
+  if (dt == 2) {
     const BundleCfg c = bundle_cfg<TrI8>(N, F, D, K, ((uintptr_t)X % 16) == 0);
     if (!c.ok) return hipErrorInvalidValue;
     const PackGeom g = pack_geom<TrI8>(F, D, 1);
@@ -1672,6 +1663,9 @@ size_t large_workspace_bytes_for(int64_t N, int64_t F, int64_t D, int64_t K, int
   const LargeCfg c =
       with_traits(dt, [&](auto tr) { return large_cfg<decltype(tr)>(N, F, D, K, x16); });
   if (!c.ok || c.ds == 1) return 0;
+  // (The slices lie at the workspace's start. The room for one counter per tile
+  // before them is no longer used, and kept so that the sizes that are accepted
+  // and refused stay the same.)
   const size_t cbytes = ((size_t)c.ntiles * sizeof(unsigned) + 255) / 256 * 256;
   return cbytes + sizeof(float) * (size_t)c.ds * N * K;
 }

@@ -270,3 +270,15 @@ def test_routes_of_new_paths(L):
     assert f32 >= 2 * 561 * 10240 * 4 + 576 * 10240 * 4
     assert b16 >= 2 * 561 * 10240 * 2 + 4 * 5 * 32 * 10240 * 2
     assert b16 < f32 // 2 + 4 * 5 * 32 * 10240 * 2
+
+
+def test_fp32_takes_the_split_kernel(L):
+    """Every fp32 HardSign call of the large-batch path and of packed training: the
+    kernels for the fp32 instruction are not built for them."""
+    for N, F, D, K in [(257, 1, 1, 1), (257, 1, 64, 128), (300, 617, 10240, 26),
+                       (1 << 20, 3072, 10240, 100), (257, 1 << 20, 448, 5),
+                       (257, 8, (1 << 22) + 64, 3), (257, 100, 5 << 20, 128)]:
+        assert L.hd_infer_kernel(N, F, D, K, hd.HD_F32, 1) in (b"large_fused_kernel_x3", b"")
+        assert L.hd_bundle_kernel(N, F, D, K, hd.HD_F32, 1) in (b"bundle_mfma_kernel_x3", b"")
+    assert L.hd_infer_kernel(257, 8, (1 << 22) + 64, 3, hd.HD_F32, 1) == b"large_fused_kernel_x3"
+    assert L.hd_bundle_kernel(1, 8, (1 << 22) + 64, 3, hd.HD_F32, 1) == b"bundle_mfma_kernel_x3"
