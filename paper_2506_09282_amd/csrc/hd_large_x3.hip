@@ -221,12 +221,12 @@ __device__ __forceinline__ bool x3_body(const X3Args& a, int tid) {
     if constexpr (RAW) {
       // past F the offset is past the matrix (zero); past column D the next row's
       // values meet zero rows of C, or are not added
-      const int off = ((16 * g + 8 * q + half) * D + 64 * u + 32 * b + col) * 4;
+      const uint32_t off = (uint32_t)((16 * g + 8 * q + half) * D + 64 * u + 32 * b + col) * 4u;
       float t[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         t[j] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(brs, off + 8 * j * D, 0, 0));
+            float, __builtin_amdgcn_raw_buffer_load_b32(brs, off + (uint32_t)(8 * j * D), 0, 0));
       v = make_float4(t[0], t[1], t[2], t[3]);
     } else {
       const int fs = 2 * g + q;
@@ -355,21 +355,22 @@ __device__ __forceinline__ bool x3_body(const X3Args& a, int tid) {
   i32x16 cacc[TRAIN ? 2 : 1][KB];       // class sums of this wave's unit
   float most = 0.0f;                    // largest |V| of all passes, or NaN
   // The C values of class block kb against the unit's dimensions.
+  const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(a.C), 0, RAW && !TRAIN ? K * D * 4 : 0, 0x00020000);
   auto c_load = [&](int u, int kb, float4 (&cv)[2][4]) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if constexpr (RAW) {
-          const int k = 32 * kb + col, d = 64 * u + 32 * b + 8 * q + 4 * half;
-          const float* cp = static_cast<const float*>(a.C) + (int64_t)min(k, K - 1) * D;
-          float t[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float c = cp[min(d + j, D - 1)];
-            t[j] = k < K && d + j < D ? c : 0.0f;
-          }
-          cv[b][q] = make_float4(t[0], t[1], t[2], t[3]);
+          // past K the offset is past the matrix (zero); past column D the next
+          // row's values, cleared
+          const int d = 64 * u + 32 * b + 8 * q + 4 * half;
+          const float4 v = __builtin_bit_cast(
+              float4, __builtin_amdgcn_raw_buffer_load_b128(
+                          crs, (uint32_t)((32 * kb + col) * D + d) * 4u, 0, 0));
+          cv[b][q] = make_float4(d < D ? v.x : 0.0f, d + 1 < D ? v.y : 0.0f,
+                                 d + 2 < D ? v.z : 0.0f, d + 3 < D ? v.w : 0.0f);
         } else {
           cv[b][q] = static_cast<const float4*>(
               a.C)[(((int64_t)(2 * u + b) * KB + kb) * 4 + q) * 64 + lane];
@@ -833,10 +834,12 @@ hipError_t launch_train(const X3Args& a, int grid, hipStream_t stream) {
                                                                stream);
 }
 
-// Offsets into B are 32-bit; row-major B is read up to 64 rows past F.
+// Offsets into B, and into C as given, are 32-bit; row-major B is read up to 64
+// rows past F, C up to 62 past K.
 bool x3_sizes_ok(int64_t F, int64_t D, int64_t K, bool raw) {
   if (cdiv(K, 32) > 4 || F > (1 << 20)) return false;
-  if (raw) return D <= (1 << 22) && F * D * 4 < ((int64_t)1 << 31);
+  if (raw)
+    return D <= (1 << 22) && F * D * 4 < ((int64_t)1 << 31) && K * D * 4 < ((int64_t)1 << 31);
   return cdiv(D, 64) * 2 * cdiv(F, 8) * 1024 < ((int64_t)1 << 31);
 }
 
