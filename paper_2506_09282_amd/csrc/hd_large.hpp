@@ -460,7 +460,7 @@ hipError_t launch_xreg(const XregPlan& p, XregArgs a, int64_t N, int dt);
 // fp32 Stage I on the bf16 matrix instruction (hd_large_x3.hip); B and C packed
 // fragments, or as given (raw). head, ds, ws as above.
 struct X3Plan {
-  int kb, ds;
+  int kb, ds, nt;  // nt: sample tiles per workgroup
   int64_t head;
   size_t ws;
   double us;  // about how long the call takes

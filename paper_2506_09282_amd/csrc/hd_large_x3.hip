@@ -36,6 +36,7 @@
 // its share of the sample tiles with one fixed unit per wave and adds each
 // tile's signs to the class sums on the int8 matrix instruction
 // (hd_train_breg.hip), which stay in registers to the end.
+#include <algorithm>
 #include <type_traits>
 
 #include "hd_large.hpp"
@@ -48,6 +49,8 @@ namespace {
 
 // Groups of 16 features per X chunk: one X item (a row's group) per thread.
 constexpr int chunk_groups(int ntiles) { return kThreads / (32 * ntiles); }
+// A pass of two tiles against one of four (the split of B is the same).
+constexpr double kTwoTilePass = 0.6;
 constexpr float kCHi = 0x1p50f;  // largest |C| in Stage II's three parts
 
 // Two floats rounded to bf16 (v_cvt_pk_bf16_f32), and the floats they stand for.
@@ -807,9 +810,6 @@ hipError_t launch_x3_kernel(const X3Args& a, int grid, size_t lds, hipStream_t s
   return hipGetLastError();
 }
 
-// Sample tiles per workgroup in inference: four, two where the scores of more
-// class blocks take the registers.
-constexpr int infer_tiles(int kb) { return kb == 1 ? 4 : 2; }
 // In training two; four with long rows and enough tiles to fill the chip (the
 // class sums at the end of a pass, with the registers full, then weigh less
 // than half the loads of B): packed N = 4096, F = 784 380 against 416 us, raw
@@ -819,9 +819,8 @@ int train_tiles(int64_t N, int64_t F, int64_t D, int kb) {
   return kb <= 2 && F >= 512 && cdiv(N, 128) * cdiv(D, 256) >= num_cus() ? 4 : 2;
 }
 
-template <int KB>
+template <int KB, int NT>
 hipError_t launch_infer(const X3Args& a, bool raw, int grid, hipStream_t stream) {
-  constexpr int NT = infer_tiles(KB);
   constexpr size_t lds = x3_lds(NT, KB, false);
   static_assert(lds <= kLdsBytes, "LDS");
   return raw ? launch_x3_kernel<&large_fused_kernel_x3<NT, KB, true>>(a, grid, lds, stream)
@@ -850,28 +849,44 @@ X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, si
   if (act != 0 || !x3_sizes_ok(F, D, K, raw)) return p;
   p.kb = kb_of(K);
   const int64_t cus = num_cus(), units = cdiv(D, 64), passes = cdiv(units, kWaves);
-  const int64_t nt = 32 * infer_tiles(p.kb), tiles = cdiv(N, nt);
-  // Whole rounds of one tile per compute unit unsplit, the tiles left over split
-  // over D: the fewest rounds, each a slice's passes and about half a pass (at
-  // F = 784) of starting and handing over. A slice has whole passes.
-  p.head = tiles / cus * cus * nt;
-  if (p.head > N) p.head = N;
-  const int64_t rest = N - p.head, rt = cdiv(rest, nt);
-  p.ds = 1;
-  const double over = 400.0 / (double)F;
-  double cost = (double)cdiv(rt, cus) * ((double)passes + over);
-  for (int ds = 2; rest > 0 && ds <= 64 && ds <= passes; ++ds) {
-    if (sizeof(float) * (size_t)ds * rest * K > ws_cap) break;
-    const double c = (double)cdiv(rt * ds, cus) * ((double)cdiv(cdiv(units, ds), kWaves) + over);
-    if (c < 0.98 * cost) {
-      cost = c;
-      p.ds = ds;
+  // Sample tiles per workgroup: four, or two, where more class blocks' scores take
+  // the registers or where the passes of four are too few for the chip (N = 500,
+  // F = 1000, D = 4096, 64 workgroups of one pass: 77 us, with two tiles 49; on the
+  // fp32 instruction 60).
+  double best = -1.0;
+  for (int nt : {4, 2}) {
+    if (nt == 4 && p.kb > 1) continue;
+    const double pass = nt == 4 ? 1.0 : kTwoTilePass;
+    const int64_t tiles = cdiv(N, 32 * nt);
+    // Whole rounds of one tile per compute unit unsplit, the tiles left over split
+    // over D: the fewest rounds, each a slice's passes and about half a pass (at
+    // F = 784) of starting and handing over. A slice has whole passes.
+    const int64_t head = std::min(N, tiles / cus * cus * 32 * nt);
+    const int64_t rest = N - head, rt = cdiv(rest, 32 * nt);
+    int ds = 1;
+    const double over = 400.0 / (double)F;
+    double cost = (double)cdiv(rt, cus) * (pass * (double)passes + over);
+    for (int d = 2; rest > 0 && d <= 64 && d <= passes; ++d) {
+      if (sizeof(float) * (size_t)d * rest * K > ws_cap) break;
+      const double c =
+          (double)cdiv(rt * d, cus) * (pass * (double)cdiv(cdiv(units, d), kWaves) + over);
+      if (c < 0.98 * cost) {
+        cost = c;
+        ds = d;
+      }
     }
+    cost += (double)(tiles / cus) * (pass * (double)passes + over);
+    if (best >= 0.0 && cost >= 0.95 * best) continue;
+    best = cost;
+    p.nt = nt;
+    p.head = head;
+    p.ds = ds;
+    p.ws = rest > 0 && ds > 1 ? sizeof(float) * (size_t)ds * rest * K : 0;
+    const double rounds =
+        pass * ((double)(tiles / cus) * (double)passes +
+                (double)cdiv(rt * ds, cus) * (double)cdiv(cdiv(units, ds), kWaves));
+    p.us = 14.0 + rounds * (1.05 * (double)cdiv(F, 16) + 5.0);
   }
-  p.ws = rest > 0 && p.ds > 1 ? sizeof(float) * (size_t)p.ds * rest * K : 0;
-  const double rounds = (double)(tiles / cus) * (double)passes +
-                        (double)cdiv(rt * p.ds, cus) * (double)cdiv(cdiv(units, p.ds), kWaves);
-  p.us = 14.0 + rounds * (1.05 * (double)cdiv(F, 16) + 5.0);
   p.ok = true;
   return p;
 }
@@ -882,10 +897,11 @@ hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* 
   auto go = [&](int64_t n0, int64_t n, int ds) {
     const X3Args a{(const float*)X + n0 * F, B, C, nullptr, labels + n0, nullptr,
                    scores ? scores + n0 * K : nullptr, (int)n, (int)F, (int)D, (int)K, ds, ws};
-    const int grid = (int)(cdiv(n, 32 * infer_tiles(p.kb)) * ds);
-    return p.kb == 1   ? launch_infer<1>(a, raw, grid, stream)
-           : p.kb == 2 ? launch_infer<2>(a, raw, grid, stream)
-                       : launch_infer<4>(a, raw, grid, stream);
+    const int grid = (int)(cdiv(n, 32 * p.nt) * ds);
+    return p.nt == 4   ? launch_infer<1, 4>(a, raw, grid, stream)
+           : p.kb == 1 ? launch_infer<1, 2>(a, raw, grid, stream)
+           : p.kb == 2 ? launch_infer<2, 2>(a, raw, grid, stream)
+                       : launch_infer<4, 2>(a, raw, grid, stream);
   };
   if (p.head > 0) {
     const hipError_t e = go(0, p.head, 1);

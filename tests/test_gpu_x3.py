@@ -92,7 +92,9 @@ def check(hd, X, B, C, seed):
 # around a unit and a pass; one, two and four class blocks
 @pytest.mark.parametrize("N,F,D,K", [(257, 1, 64, 3), (257, 15, 65, 32), (300, 16, 256, 33),
                                      (384, 17, 257, 64), (385, 63, 320, 65), (300, 64, 500, 128),
-                                     (300, 65, 1000, 10), (513, 130, 96, 5), (300, 1277, 300, 26)])
+                                     (300, 65, 1000, 10), (513, 130, 96, 5), (300, 1277, 300, 26),
+                                     # 64- and 128-sample tiles of one class block
+                                     (2000, 40, 1100, 3), (4100, 33, 2100, 32)])
 def test_integer_bit_exact(hd, N, F, D, K):
     announce(f"x3 N={N} F={F} D={D} K={K}")
     check(hd, *wide_ints(N, F, D, K, N + F), seed=F)
