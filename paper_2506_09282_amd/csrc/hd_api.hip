@@ -276,7 +276,7 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
     if (dry) return HD_OK;
     return from_hip(
         hd::launch_large(X, packed, labels, scores, N, F, D, K, dt, act, workspace,
-                         det ? least : workspace_bytes, stream));
+                         det ? least : workspace_bytes, nullptr, stream));
   }
   // Raw matrices: the scratch that must start at zero (tile counters, split-D
   // partial scores) stays at offset 0, the same place every route keeps it, and
@@ -296,10 +296,11 @@ static hd_status infer_common(const void* X, const void* B, const void* C, const
     return from_hip(err);
   char* copy = static_cast<char*>(workspace) + zone;
   if (hd::launch_pack(B, C, F, D, K, dt, copy, stream) != hipSuccess) return HD_ERR_HIP;
-  const hipError_t e =
-      hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace, cap, stream);
+  hd::Clear clear{copy, pb / 16};  // (whole fragments of 1 KiB)
+  const hipError_t e = hd::launch_large(X, copy, labels, scores, N, F, D, K, dt, act, workspace,
+                                        cap, &clear, stream);
   if (e != hipSuccess) return HD_ERR_HIP;
-  return from_hip(hd::launch_zero(copy, pb, stream));
+  return clear.n > 0 ? from_hip(hd::launch_zero(copy, pb, stream)) : HD_OK;
 }
 
 hd_status hd_infer(const void* X, const void* B, const void* C, int32_t* labels, float* scores,
@@ -359,7 +360,7 @@ hd_status hd_infer_stream(const void* X, const void* packed, const uint32_t* rea
   // batch by batch, each waiting for its X and its hand-off, 470 us so).
   if (!ready && !done && hd::stream_as_one_batch(nbatch, N, F, D, K, act, workspace_bytes))
     return from_hip(hd::launch_large(X, packed, labels, scores, nbatch * N, F, D, K, dt, act,
-                                     workspace, workspace_bytes, stream));
+                                     workspace, workspace_bytes, nullptr, stream));
   const char* small = static_cast<const char*>(packed) + image_layout(F, D, K, dt).large;
   return from_hip(hd::launch_stream(X, small, ready, labels, scores, done, nbatch, N, F, D, K,
                                     act, workspace, stream));

@@ -133,9 +133,14 @@ size_t large_workspace_used(const void* X, int64_t N, int64_t F, int64_t D, int6
                             int act, size_t ws_bytes);
 hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64_t K, int dt,
                        void* packed, hipStream_t stream);
+// clear: 16-byte words that the call's last launch clears if it can (n is then 0).
+struct Clear {
+  void* p;
+  size_t n;
+};
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
-                        void* workspace, size_t ws_bytes, hipStream_t stream);
+                        void* workspace, size_t ws_bytes, Clear* clear, hipStream_t stream);
 // Whether a stream whose batches are all present, and whose batches nobody
 // counts, is faster as one batch on the large-batch kernels (fp32).
 bool stream_as_one_batch(int64_t nbatch, int64_t N, int64_t F, int64_t D, int64_t K, int act,

@@ -33,6 +33,7 @@
 // 4-byte aligned, up to 16 samples of one class block; training: more than 40). fp32
 // with HardSign runs in hd_large_x3.hip, training too. The packing and the entry
 // points of the path are here.
+#include <algorithm>
 #include <type_traits>
 
 #include "hd_large.hpp"
@@ -176,11 +177,21 @@ __global__ void pack_c_f32(const float* __restrict__ C, uint4* __restrict__ Cp, 
 // loads, one latency after the other: 9 us). A last-arriver reduction inside the
 // main kernel has one workgroup per sample tile read every slice with
 // returning atomics: at N = 4096, F = 617, K = 26 (bf16, 16 slices) that call
-// took 135 us.
+// took 135 us. Workgroups past the rows' clear the packed copy that a call with B
+// and C as given made in its workspace, which saves it a launch.
 __global__ __launch_bounds__(1024) void reduce_slices_kernel(float* __restrict__ part,
                                                             int32_t* __restrict__ labels,
                                                             float* __restrict__ scores, int N,
-                                                            int K, int ds) {
+                                                            int K, int ds, uint4* __restrict__ clear,
+                                                            int64_t nclear) {
+  const int nreduce = (int)cdiv(N, 256 / K);
+  if ((int)blockIdx.x >= nreduce) {
+    const int64_t step = (int64_t)(gridDim.x - nreduce) * blockDim.x;
+    for (int64_t j = (int64_t)(blockIdx.x - nreduce) * blockDim.x + threadIdx.x; j < nclear;
+         j += step)
+      clear[j] = make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
   __shared__ float group_sum[3][256], row[256];
   const int rpw = 256 / K, tid = threadIdx.x & 255;
   const int group = threadIdx.x >> 8, groups = blockDim.x >> 8;
@@ -1442,7 +1453,7 @@ hipError_t launch_act(const LargeCfg& c, const void* X, const uint4* Bp, const u
 template <class Tr, int NTILES, int KB>
 hipError_t launch_cfg(const LargeCfg& c, const void* X, const uint4* Bp, const uint4* Cp,
                       int32_t* labels, float* scores, int64_t N, int64_t F, int64_t K, int ndb,
-                      int act, void* ws, hipStream_t stream) {
+                      int act, void* ws, Clear* clear, hipStream_t stream) {
   // (fp32 with HardSign: the split kernel takes all sizes that large_cfg does)
   hipError_t e = hipErrorInvalidValue;
   if (act)
@@ -1450,13 +1461,13 @@ hipError_t launch_cfg(const LargeCfg& c, const void* X, const uint4* Bp, const u
   else if constexpr (Tr::kEsz <= 2)
     e = launch_act<Tr, NTILES, KB, 0>(c, X, Bp, Cp, labels, scores, N, F, K, ndb, ws, stream);
   if (e != hipSuccess || c.ds == 1) return e;
-  return launch_reduce_slices(ws, labels, scores, N, K, c.ds, stream);
+  return launch_reduce_slices(ws, labels, scores, N, K, c.ds, clear, stream);
 }
 
 template <class Tr>
 hipError_t launch_tr(const void* X, const void* packed, int32_t* labels, float* scores,
                      int64_t N, int64_t F, int64_t D, int64_t K, int act, void* ws,
-                     size_t ws_bytes, hipStream_t stream) {
+                     size_t ws_bytes, Clear* clear, hipStream_t stream) {
   const LargeCfg c = large_cfg<Tr>(N, F, D, K, ((uintptr_t)X % 16) == 0);
   if (!c.ok) return hipErrorInvalidValue;
   const PackGeom g = pack_geom<Tr>(F, D, K);
@@ -1466,17 +1477,19 @@ hipError_t launch_tr(const void* X, const void* packed, int32_t* labels, float* 
     constexpr int dt = Tr::kEsz == 2 ? 1 : 2;
     const XregPlan p = xreg_plan(N, F, D, K, dt, act, (uintptr_t)X % 4 == 0, ws_bytes);
     if (p.ok)
-      return launch_xreg(p, XregArgs{X, Bp, Cp, labels, scores, (int)F, (int)K, g.ndb, ws, stream},
+      return launch_xreg(p, XregArgs{X, Bp, Cp, labels, scores, (int)F, (int)K, g.ndb, ws, clear,
+                                     stream},
                          N, dt);
   } else {
     const X3Plan p = x3_plan(N, F, D, K, act, false, ws_bytes);
     if (p.ok)
-      return launch_x3(p, X, Bp, Cp, false, labels, scores, N, F, D, K, ws, stream);
+      return launch_x3(p, X, Bp, Cp, false, labels, scores, N, F, D, K, ws, clear, stream);
   }
   const int nt = c.ntiles_per_wg, kb = c.kb;
 #define HD_LAUNCH(NTV, KBV)                                                                       \
   if (nt == NTV && kb == KBV)                                                                     \
-    return launch_cfg<Tr, NTV, KBV>(c, X, Bp, Cp, labels, scores, N, F, K, g.ndb, act, ws, stream);
+    return launch_cfg<Tr, NTV, KBV>(c, X, Bp, Cp, labels, scores, N, F, K, g.ndb, act, ws, clear, \
+                                    stream);
   HD_LAUNCH(4, 1)
   HD_LAUNCH(4, 2)
   HD_LAUNCH(2, 1)
@@ -1580,10 +1593,15 @@ hipError_t launch_bundle_dma(const BundleCfg& c, const void* X, const void* pack
 
 namespace lg {
 hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
-                                int ds, hipStream_t stream) {
-  hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)cdiv(N, 256 / K)),
-                     dim3(256u * (ds > 48 ? 4 : ds > 32 ? 3 : ds > 16 ? 2 : 1)), 0, stream,
-                     (float*)ws, labels, scores, (int)N, (int)K, ds);
+                                int ds, Clear* clear, hipStream_t stream) {
+  const unsigned threads = 256u * (ds > 48 ? 4 : ds > 32 ? 3 : ds > 16 ? 2 : 1);
+  // (up to 4096 workgroups: one round of stores)
+  const int64_t n = clear ? (int64_t)clear->n : 0;
+  const int64_t cgrid = std::min<int64_t>(cdiv(n, threads), 4096);
+  hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)(cdiv(N, 256 / K) + cgrid)),
+                     dim3(threads), 0, stream, (float*)ws, labels, scores, (int)N, (int)K, ds,
+                     n > 0 ? (uint4*)clear->p : nullptr, n);
+  if (clear) clear->n = 0;
   return hipGetLastError();
 }
 }  // namespace lg
@@ -1703,7 +1721,7 @@ bool launch_large_raw(const void* X, const void* B, const void* C, int32_t* labe
   if (dt != 0) return false;
   const X3Plan p = x3_plan(N, F, D, K, act, true, ws_bytes);
   if (!p.ok) return false;
-  *err = launch_x3(p, X, B, C, true, labels, scores, N, F, D, K, workspace, stream);
+  *err = launch_x3(p, X, B, C, true, labels, scores, N, F, D, K, workspace, nullptr, stream);
   return true;
 }
 
@@ -1752,10 +1770,10 @@ hipError_t launch_pack(const void* B, const void* C, int64_t F, int64_t D, int64
 
 hipError_t launch_large(const void* X, const void* packed, int32_t* labels, float* scores,
                         int64_t N, int64_t F, int64_t D, int64_t K, int dt, int act,
-                        void* workspace, size_t ws_bytes, hipStream_t stream) {
+                        void* workspace, size_t ws_bytes, Clear* clear, hipStream_t stream) {
   return with_traits(dt, [&](auto tr) {
     return launch_tr<decltype(tr)>(X, packed, labels, scores, N, F, D, K, act, workspace,
-                                   ws_bytes, stream);
+                                   ws_bytes, clear, stream);
   });
 }
 

@@ -361,7 +361,7 @@ __device__ __forceinline__ float* slice_part(void* ws, int slice, int N, int K) 
   return reinterpret_cast<float*>(ws) + (int64_t)slice * N * K;
 }
 hipError_t launch_reduce_slices(void* ws, int32_t* labels, float* scores, int64_t N, int64_t K,
-                                int ds, hipStream_t stream);
+                                int ds, Clear* clear, hipStream_t stream);
 
 // Combine the waves' partial scores through LDS, then argmax (Eq. 9) and
 // write; with a split of D, leave this slice's partial scores for
@@ -450,6 +450,7 @@ struct XregArgs {
   float* scores;
   int F, K, ndb;
   void* workspace;
+  Clear* clear;
   hipStream_t stream;
 };
 // The plan within ws_cap bytes of workspace; x4: X is 4-byte aligned.
@@ -469,6 +470,6 @@ struct X3Plan {
 X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, size_t ws_cap);
 hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* C, bool raw,
                      int32_t* labels, float* scores, int64_t N, int64_t F, int64_t D, int64_t K,
-                     void* ws, hipStream_t stream);
+                     void* ws, Clear* clear, hipStream_t stream);
 
 }  // namespace hd

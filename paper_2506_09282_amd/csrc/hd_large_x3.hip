@@ -893,7 +893,7 @@ X3Plan x3_plan(int64_t N, int64_t F, int64_t D, int64_t K, int act, bool raw, si
 
 hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* C, bool raw,
                      int32_t* labels, float* scores, int64_t N, int64_t F, int64_t D, int64_t K,
-                     void* ws, hipStream_t stream) {
+                     void* ws, Clear* clear, hipStream_t stream) {
   auto go = [&](int64_t n0, int64_t n, int ds) {
     const X3Args a{(const float*)X + n0 * F, B, C, nullptr, labels + n0, nullptr,
                    scores ? scores + n0 * K : nullptr, (int)n, (int)F, (int)D, (int)K, ds, ws};
@@ -910,7 +910,7 @@ hipError_t launch_x3(const X3Plan& p, const void* X, const void* B, const void* 
   const hipError_t e = go(p.head, N - p.head, p.ds);
   if (e != hipSuccess || p.ds == 1) return e;
   return launch_reduce_slices(ws, labels + p.head, scores ? scores + p.head * K : nullptr,
-                              N - p.head, K, p.ds, stream);
+                              N - p.head, K, p.ds, clear, stream);
 }
 
 // Not by N: a training set fed in chunks gets the signs, and so the counts, of one

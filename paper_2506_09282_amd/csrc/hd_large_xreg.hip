@@ -455,7 +455,8 @@ hipError_t launch_xreg(const XregPlan& p, XregArgs a, int64_t N, int dt) {
   if (a.scores) a.scores += p.head * a.K;
   const hipError_t e = go(N - p.head, p.ds);
   if (e != hipSuccess || p.ds == 1) return e;
-  return launch_reduce_slices(a.workspace, a.labels, a.scores, N - p.head, a.K, p.ds, a.stream);
+  return launch_reduce_slices(a.workspace, a.labels, a.scores, N - p.head, a.K, p.ds, a.clear,
+                              a.stream);
 }
 
 }  // namespace hd
