@@ -324,6 +324,12 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 
 typedef int rsrc_t __attribute__((ext_vector_type(4)));
 
+// What v was read from is done with: the compiler waits for the read here, before
+// any later assembly (a barrier after which other waves write there).
+__device__ __forceinline__ void have(const uint4& v) {
+  asm volatile("" ::"v"(bitcast<i32x4>(v)));
+}
+
 // 1 KiB from global memory straight into LDS: lane l's 16 bytes at byte offset
 // `off` of the buffer land at lds + 16 l; offsets past the buffer's end
 // deliver zeros. Issued as assembly so that the compiler does not take every

@@ -245,6 +245,14 @@ __global__ __launch_bounds__(kThreads, 1) void large_fused_kernel_xreg(
         }
         constexpr int kStep = NFS >= 20 ? (NFS / 2 - 6) / 4 : 1;  // steps between the four pieces
         constexpr int kS0 = NFS >= 12 ? 4 : 2;
+        static_assert(kS0 + kStep < MID, "slot slp is read before the barrier that frees it");
+        if (s == kS0 + kStep) {
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) {
+            have(cf[0][kb]);
+            have(cf[1][kb]);
+          }
+        }
         if (s >= kS0 && s < kS0 + 4 * kStep && (s - kS0) % kStep == 0) {
           const int p = (s - kS0) / kStep, t = p >> 1, h = p & 1;
           uint4 hb;

@@ -290,6 +290,11 @@ __device__ __forceinline__ void bundle_breg(const BregArgs& a) {
       ring[s % DP] = *reinterpret_cast<const uint4*>(s + DP < NFS ? fr + (s + DP) * 1024
                                                                   : fn + (s + DP - NFS) * 1024);
       if constexpr (!kFirst) {
+        static_assert(2 < MID, "slot slp is read before the barrier that frees it");
+        if (s == 2) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) have(bitcast<uint4>(yl[q]));
+        }
 #pragma unroll
         for (int t = (s - 1) * kPer; t < s * kPer; ++t)
           if (t >= 0 && t < kTasks) task(t);
