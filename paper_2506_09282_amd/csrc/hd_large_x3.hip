@@ -10,23 +10,26 @@
 // by truncation: up to 2^-21, always towards zero). Six such instructions cost 192
 // cycles for 16 features against 512 of the fp32 instruction.
 // Against 64 bits, signs of X B that differ in 1e9 (normal X; the fp32 instruction
-// 32x32x2 in brackets): F = 4 1.0 (4.2), 16 1.9 (12.7), 32 2.9 (17.0), 100 10 (22),
-// 300 11 (47), 561 19 (75; the streaming kernel's 16x16x4 40), 784 22 (87), 1500
-// 32 (114).
+// 32x32x2 in brackets): F = 2 1.5 (2.2), 4 0.8 (3.7), 16 2.2 (15), 32 2.6 (15), 100
+// 10 (26), 300 14 (49), 561 25 (70; the streaming kernel's 16x16x4 40), 784 22 (84),
+// 1500 35 (113), 3072 55 (174).
 //
 // Measured (fp32 instruction in brackets; us): inference D = 10240 N = 4096,
-// F = 784, K = 10 packed 317 (601), raw N = 500, F = 617, D = 10000, K = 26 69
-// (151); N = 20000, F = 784 1570 (3506); training N = 4096, F = 784 380 (915),
-// raw 441 (1648, fp32 vector units). About 1.25 PFLOP/s of bf16 products, at the
-// 1.9 GHz that this leaves of the clock.
+// F = 784, K = 10 packed 334 (601), raw N = 500, F = 617, D = 10000, K = 26 65
+// (151); N = 20000, F = 784 1590 (3546); training N = 4096, F = 784 358 (916),
+// raw 397 (1638, fp32 vector units), raw N = 2048 195 (804). About 1.25 PFLOP/s of
+// bf16 products, at the 1.9 GHz that this leaves of the clock.
 //
 // Range. A value with bits below 2^-133 (some values below 2^-110) is not the sum
 // of its parts, inf has no parts, the largest values round to it, and near 2^128
 // the order of a sum decides. So the bits of trailing parts are gathered in the
 // split (one instruction for two values), and the largest sum where its sign is
-// taken; a workgroup that saw such a value, or a sum that is not finite, does its
-// passes again and takes the sums concerned from the fp32 instruction (CAREFUL,
-// below). Both instructions take and give subnormal numbers.
+// taken. A workgroup that saw such a value, or a sum that is not finite and not
+// explained by NaN alone, does its passes again and takes the sums concerned from
+// the fp32 instruction (CAREFUL, below). Both instructions take and give subnormal
+// numbers. N = 4096, F = 784, us (all on the fp32 instruction in brackets): inference
+// one row with inf 1300 (604), 1% of the rows with NaN 395 (602), all of X subnormal 1310
+// (602); training 907 (917), 405 (919), 1560 (916).
 //
 // Work split. A workgroup holds a tile of 32 NTILES samples; each wave takes one
 // unit of 64 dimensions per pass. B comes from L2 straight into registers (each
@@ -49,9 +52,11 @@ namespace {
 
 // Groups of 16 features per X chunk: one X item (a row's group) per thread.
 constexpr int chunk_groups(int ntiles) { return kThreads / (32 * ntiles); }
-// A pass of two tiles against one of four (the split of B is the same).
+// A pass of two tiles against one of four, the split of B being the same (N = 10000,
+// F = 784: 1000 us with two, 866 with four).
 constexpr double kTwoTilePass = 0.6;
 constexpr float kCHi = 0x1p50f;  // largest |C| in Stage II's three parts
+constexpr float kHi = 0x1p50f;   // |X|, |B| up to which no sum of 2^20 products overflows
 
 // Two floats rounded to bf16 (v_cvt_pk_bf16_f32), and the floats they stand for.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -100,6 +105,27 @@ __device__ __forceinline__ void split8(const float4& a, const float4& b, uint4 (
 
 // Order of the six products, parts of B and of X: lh, mh, mm, hh, hm, hl.
 constexpr int kPartB[6] = {2, 1, 1, 0, 0, 0}, kPartX[6] = {0, 0, 1, 0, 1, 2};
+
+// Largest magnitude but NaN among the 16-byte words at byte offsets offset_of(0),
+// offset_of(1), ... of p, over a workgroup's threads; to the first offset past the end.
+template <class Fn>
+__device__ __forceinline__ float largest(const float* p, int64_t bytes, int tid, Fn&& offset_of) {
+  constexpr int kBatch = 16;  // loads in flight
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(p), 0, (int)bytes, 0x00020000);
+  float m = 0.0f;
+  for (uint32_t i = tid; offset_of(i - tid) < bytes; i += kBatch * kThreads) {
+    float4 v[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      v[j] = __builtin_bit_cast(
+          float4, __builtin_amdgcn_raw_buffer_load_b128(rs, offset_of(i + j * kThreads), 0, 0));
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(v[j].x), fabsf(v[j].y)), fmaxf(fabsf(v[j].z), fabsf(v[j].w))));
+  }
+  return m;
+}
 
 struct X3Args {
   const float* X;
@@ -743,7 +769,36 @@ __device__ __forceinline__ bool x3_body(const X3Args& a, int tid) {
     uint32_t rest = restb[0] | restb[1];
 #pragma unroll
     for (int i = 0; i < IPT; ++i) rest |= restx[i];
-    if (__syncthreads_or((rest & 0xffffu) || !(most < __builtin_huge_valf()))) return true;
+    if (__syncthreads_or(rest & 0xffffu)) return true;
+    if (__builtin_expect(__syncthreads_or(!(most < __builtin_huge_valf())), 0)) {
+      // NaN in X or B makes its sums NaN on either instruction. Without inf or values
+      // that could overflow there is nothing else.
+      int first = tid;  // (a thread index of this part's own: see x3_kernel)
+      asm volatile("" : "+v"(first));
+      float big = 0.0f;  // largest magnitude but NaN
+      for (int t = t_begin; t < t_end; ++t) {
+        const int64_t n0 = (int64_t)t * NT;
+        const int64_t count = min((int64_t)NT, (int64_t)N - n0) * F;
+        big = fmaxf(big, largest(a.X + n0 * F, count * 4, first, [](uint32_t i) { return 16u * i; }));
+      }
+      const float* B = static_cast<const float*>(a.B);
+      if constexpr (RAW) {
+        // rows of the slice's columns, four at a time
+        const uint32_t words = 16u * (u_end - u_begin);
+        big = fmaxf(big, largest(B + 64 * u_begin, ((int64_t)F * D - 64 * u_begin) * 4, first,
+                                 [&](uint32_t i) {
+                                   const uint32_t f = i / words;
+                                   return f < (uint32_t)F
+                                              ? (f * (uint32_t)D + 4u * (i - f * words)) * 4u
+                                              : 0xfffffff0u;
+                                 }));
+      } else {
+        const int64_t per = (int64_t)2 * nfs8 * 256;  // floats per unit
+        big = fmaxf(big, largest(B + u_begin * per, (u_end - u_begin) * per * 4, first,
+                                 [](uint32_t i) { return 16u * i; }));
+      }
+      if (__syncthreads_or(big > kHi)) return true;
+    }
   }
 
   if constexpr (TRAIN) {
@@ -810,11 +865,11 @@ hipError_t launch_x3_kernel(const X3Args& a, int grid, size_t lds, hipStream_t s
   return hipGetLastError();
 }
 
-// In training two; four with long rows and enough tiles to fill the chip (the
-// class sums at the end of a pass, with the registers full, then weigh less
-// than half the loads of B): packed N = 4096, F = 784 380 against 416 us, raw
-// N = 2048 205 against 235 us, but F = 100, N = 10000 262 against 207 us and
-// N = 300, F = 617 56 against 33 us.
+// Sample tiles per workgroup in training: two; four with long rows and enough tiles
+// to fill the chip (the class sums at the end of a pass, with the registers full,
+// then weigh less than half the loads of B): packed N = 4096, F = 784 357 against 383
+// us, raw N = 2048 201 against 222 us, but F = 100, N = 10000 196 against 178 us and
+// N = 300, F = 617 49 against 30 us.
 int train_tiles(int64_t N, int64_t F, int64_t D, int kb) {
   return kb <= 2 && F >= 512 && cdiv(N, 128) * cdiv(D, 256) >= num_cus() ? 4 : 2;
 }

@@ -142,6 +142,28 @@ def test_training_sizes(hd, N, F, D, K):
         assert np.array_equal(c.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("where", ["X", "B", "X, huge", "B, huge"])
+def test_nan(hd, where):
+    """NaN makes the sums of its row or column NaN (HardSign -1) and needs no other
+    instruction, unless there is more: here products that overflow."""
+    announce(f"x3 NaN in {where}")
+    N, F, D, K = 300, 70, 600, 5
+    X, B, C = hd_inputs.make_integer_inputs(N, F, D, K, seed=21)
+    if "huge" in where:
+        # one product per sum, of 16-bit values, beyond 2^136: infinite on the fp32
+        # instruction, inf - inf as a sum of parts
+        n = np.arange(N)
+        one = np.zeros_like(X)
+        one[n, n % F] = np.where(X[n, n % F] < 0, -1, 1)
+        X, B = one * np.float32(2.0 ** 70 * 1.0078125), B * np.float32(2.0 ** 66 * 1.0234375)
+        B[B == 0] = 1.0
+    if where.startswith("X"):
+        X[[3, 129, 299], [0, 69, 5]] = np.nan
+    else:
+        B[[0, 69, 5], [1, 300, 599]] = np.nan
+    check(hd, X, B, C, seed=21)
+
+
 @pytest.mark.parametrize("what", ["inf", "tiny row", "huge b"])
 def test_training_range(hd, what):
     """The fall back to the fp32 instruction, with tiles after it."""
